@@ -52,6 +52,14 @@ int launch_block_pair(const LaunchArgs &fwd, const LaunchArgs &rev, bool commit,
 int launch_conv_fused(const LaunchArgs &a, const float *w, const float *bias, const float *conv_pool,
                       bool commit, bool want_y, void *stream);
 
+// The same on any block of up to 256 tokens (bf16 or fp32 inputs) whose Gram tiles and split
+// operands fit in the convolution workspace (mix_fits; ws: conv_workspace bytes): a Gram
+// kernel per (row, group), then one workgroup per (row, head) computing both branches; a
+// commit also replaces the cached input rows.  a.y may be nullptr for a commit.
+bool mix_fits(const LaunchArgs &a);
+int launch_mix(const LaunchArgs &a, const float *w, const float *bias, float *conv_pool, bool commit,
+               void *ws, void *stream);
+
 // How the sequence kernels cut T tokens into segments (one workgroup per batch row,
 // head and segment) and the device workspace they need: per (row, head, segment)
 // `dirs` states of 64 x dstate fp32, then one fp32 log-decay, rounded up to 256

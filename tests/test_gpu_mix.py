@@ -1,0 +1,69 @@
+"""GPU parity of the convolution-state step and commit on the Gram and head kernels
+(bdlm_mix.hip: blocks of up to 256 tokens that the block kernel's staging does not take),
+at the edges of their tiles: lengths around 16-token tiles, 32-token pairs, 64-, 128- and
+256-token blocks, every dstate, both storage types, several groups, slot maps, decays that
+underflow within a pair of tiles, and a shape whose tiles do not fit in the workspace (which
+takes the convolution kernel and the scan kernels).  Oracle and bar as in test_gpu_conv.py.
+"""
+import numpy as np
+import pytest
+import torch
+
+import bdlm_inputs as bi
+import oracle
+from tests.gpu_util import DEV, REL_TOL, from_pool, pool_dev, rel_err, to_dev
+from tests.test_gpu_conv import conv_params, oracle_step, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H,N,L,bf16,G,fast,want_y", [
+    (4, 128, 33, True, 1, False, True), (3, 16, 64, True, 1, True, True),
+    (6, 64, 65, False, 2, False, True), (5, 32, 128, True, 1, False, False),
+    (4, 128, 129, False, 1, True, True), (8, 64, 255, True, 2, False, True),
+    (26, 128, 256, True, 1, False, True), (4, 32, 256, True, 1, True, True),
+    (4, 16, 160, True, 1, False, False), (4, 128, 17, False, 1, False, True),
+    (4, 128, 64, True, 1, True, True),
+    (2, 128, 256, True, 2, False, True),       # one head per group: the tiles do not fit
+])
+def test_conv_long_blocks(H, N, L, bf16, G, fast, want_y):
+    import paper_2607_02805_amd as bd
+    w = bi.Workload("t", 2, H, 64, N, G, L, 0, bf16, 1, 12000 + H + N + L)
+    d, c = bi.block_inputs(w, 0), bi.commit_inputs(w)
+    d["D_rev"] = (d["D"] * 0.5).astype(np.float32)
+    c["D_rev"] = d["D_rev"]
+    if fast:     # a token's decay reaches 2^-60: products of decays underflow
+        for v in (d, c):
+            v["dt"] = bi.to_bf16_bits(bi.bf16_bits_to_f32(v["dt"]) * np.float32(300.0)) if bf16 \
+                else v["dt"] * np.float32(300.0)
+    cw, cb = conv_params(w, 12100 + L)
+    cache = np.random.Generator(np.random.PCG64(5)).standard_normal((4, 3, cw.shape[0])).astype(np.float32)
+    pool = bi.random_state(w, 4, 6, 0.5).astype(np.float64)
+    cwd, cbd = torch.from_numpy(cw).to(DEV), torch.from_numpy(cb).to(DEV)
+    cp, h = torch.from_numpy(cache).to(DEV), pool_dev(pool)
+    say("conv block", dict(H=H, N=N, L=L, bf16=bf16, G=G, fast=fast))
+    v = to_dev(d)
+    y = bd.conv_block_step(v["x"], v["dt"], v["A"], v["B"], v["C"], v["D"], v["D_rev"], cwd, cbd, cp, h,
+                           slot_idx=[3, 3])
+    torch.cuda.synchronize()
+    y_ref, _ = oracle_step(d, cw, cb, cache.astype(np.float64), pool, [3, 3])
+    e = rel_err(y, y_ref)
+
+    slots = [2, 0]
+    y_ref, fin = oracle_step(c, cw, cb, cache.astype(np.float64), pool, slots)
+    *_, s_ref = oracle.block_step(fin, pool, slot_idx=slots, parts=True, final_state=True)
+    cache_ref = cache.astype(np.float64)
+    oracle.conv(c, cw, cb, cache_ref, slot_idx=slots, commit=True)
+    nc, nb = np.zeros(4, np.int64), np.zeros(4, np.int64)
+    v = to_dev(c)
+    yc = bd.conv_commit_boundary(v["x"], v["dt"], v["A"], v["B"], v["C"], v["D"], v["D_rev"], cwd, cbd, cp,
+                                 h, nc, nb, 0, slot_idx=slots, y_clean=True if want_y else None)
+    torch.cuda.synchronize()
+    got = from_pool(h)
+    es = rel_err(got[slots], s_ref)
+    ey = rel_err(yc, y_ref) if want_y else 0.0
+    say("  rel err step", e, "state", es, "clean y", ey)
+    assert max(e, es, ey) <= REL_TOL
+    np.testing.assert_array_equal(got[[1, 3]], pool[[1, 3]].astype(np.float32))   # untouched slots
+    np.testing.assert_array_equal(cp.cpu().numpy(), cache_ref.astype(np.float32))
+    assert nc.tolist() == [L, 0, L, 0] and nb.tolist() == [1, 0, 1, 0]
