@@ -17,6 +17,10 @@
 //   seg_out      the outputs of each segment in 64-token chunks from its entering state
 //                (the reverse pass reads the forward pass's outputs a chunk at a time
 //                and stores the sums: one reader and writer per element, no atomics).
+// bf16 activations take the kernels of bdlm_seq16.hip for the segment states, for both branches
+// of a full window or a long block, and for forward outputs with enough row-heads; here run
+// fp32 activations, and in bf16 the other forward passes (among them all that emit block
+// states) and the reverse pass of a step whose reverse branch has inputs of its own.
 // The reverse direction is the forward scan of the time-reversed sequence (every
 // token keeps its own x, dt, B, C), so seg_out loads each chunk flipped and walks
 // the segment's chunks backwards with the forward arithmetic.
@@ -43,6 +47,7 @@
 #include "bdlm.h"
 #include "bdlm_device.h"
 #include "bdlm_launch.h"
+#include "bdlm_seq.h"
 
 namespace bdlm {
 namespace {
@@ -50,36 +55,6 @@ namespace {
 constexpr int kC = 64;           // chunk length (tokens): one token per lane in the scan
 constexpr int kThreads = 256;    // 4 waves
 constexpr int kTiles = 10;       // lower-triangle 16x16 tiles of a 64x64 chunk
-
-struct SeqArgs {
-    const void *x, *dt, *Bm, *Cm;
-    const float *A, *skip;       // skip: D (forward) or D_rev (reverse)
-    float *y;                    // seg_out: outputs; nullptr: none
-    float *ws;                   // segment states [unit][seg][dirs][64 * N] (pool layout)
-    float *tot;                  // segment log2-decays [unit][seg]
-    int64_t xs_b, xs_t, xs_h;
-    int64_t dts_b, dts_t;
-    int64_t bcs_b, bcs_t, bcs_g;
-    int64_t T, S;                // tokens in the sequence; tokens per segment
-    int32_t nseg, dirs;
-    int32_t nheads, heads_per_group;
-    int32_t zero_init;           // seg_out: every segment starts from zero (ws unused)
-    int32_t xcd_remap;           // grid % 8 == 0: keep a (row, segment)'s heads on one XCD
-    int32_t blk_major;           // states of (row, head, segment) at slot (row * nseg + segment)
-                                 // * nheads + head (a pool of per-block states); else
-                                 // (row * nheads + head) * nseg + segment
-    // seg_out with one segment per row (a block step or commit of any length):
-    const float *pool_in;        // the entering state from the cache (slot per row)
-    float *pool_out;             // the final state written back to the cache (in place)
-    // seg_out, forward: chunks of cstride (<= 64) tokens, and the state entering every
-    // chunk written to emit[(row * emit_blocks + block) * nheads + head] (block = the
-    // chunk's index in the sequence; segments hold whole chunks)
-    int32_t cstride;
-    float *emit;
-    int64_t emit_blocks;
-    int32_t use_slots;
-    int32_t slots[BDLM_MAX_SLOT_ROWS];
-};
 
 // Slot of workgroup (row, head, segment)'s states in ws (times dirs states each).
 __device__ __forceinline__ int64_t state_slot(const SeqArgs &a, int b, int h, int seg) {
@@ -460,8 +435,10 @@ __device__ __forceinline__ void setup(ST &st, const SeqArgs &a, const Unit &un, 
 // ------------------------------------------------------------------ seg_state
 // Local forward state F (and, BOTH, reverse state R) of one segment from zero, and
 // the segment's total log2-decay.
-template <int NS, bool F32, bool BOTH>
-__global__ void __launch_bounds__(kThreads, F32 ? 1 : 2) bdlm_seg_state_kernel(const SeqArgs a) {
+// (fp32 storage; bf16 runs on bdlm_seg_state16_kernel)
+template <int NS, bool BOTH>
+__global__ void __launch_bounds__(kThreads, 1) bdlm_seg_state_kernel(const SeqArgs a) {
+    constexpr bool F32 = true;
     using G = Geo<NS, F32>;
     constexpr int QN = G::QN;
     // B: bf16 row image (read transposed) or fp32 transposed image; x likewise
@@ -1017,12 +994,12 @@ __global__ void __launch_bounds__(256) bdlm_seg_combine_kernel(const CombineArgs
 }
 
 // ------------------------------------------------------------------ host side
-template <int NS, bool F32>
+template <int NS>
 hipError_t state_launch(const SeqArgs &k, bool both, unsigned grid, hipStream_t s) {
     if (both)
-        hipLaunchKernelGGL((bdlm_seg_state_kernel<NS, F32, true>), dim3(grid), dim3(kThreads), 0, s, k);
+        hipLaunchKernelGGL((bdlm_seg_state_kernel<NS, true>), dim3(grid), dim3(kThreads), 0, s, k);
     else
-        hipLaunchKernelGGL((bdlm_seg_state_kernel<NS, F32, false>), dim3(grid), dim3(kThreads), 0, s, k);
+        hipLaunchKernelGGL((bdlm_seg_state_kernel<NS, false>), dim3(grid), dim3(kThreads), 0, s, k);
     return hipGetLastError();
 }
 template <int NS, bool F32>
@@ -1049,13 +1026,12 @@ hipError_t out_sub_launch(const SeqArgs &k, int sub, unsigned grid, hipStream_t 
     return hipGetLastError();
 }
 
-template <bool F32>
-hipError_t run_state(int ns, const SeqArgs &k, bool both, unsigned grid, hipStream_t s) {
+hipError_t run_state_f32(int ns, const SeqArgs &k, bool both, unsigned grid, hipStream_t s) {
     switch (ns) {
-        case 16: return state_launch<16, F32>(k, both, grid, s);
-        case 32: return state_launch<32, F32>(k, both, grid, s);
-        case 64: return state_launch<64, F32>(k, both, grid, s);
-        case 128: return state_launch<128, F32>(k, both, grid, s);
+        case 16: return state_launch<16>(k, both, grid, s);
+        case 32: return state_launch<32>(k, both, grid, s);
+        case 64: return state_launch<64>(k, both, grid, s);
+        case 128: return state_launch<128>(k, both, grid, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -1080,6 +1056,41 @@ hipError_t run_out(int ns, const SeqArgs &k, bool rev, unsigned grid, hipStream_
     }
 }
 
+// One launch over the segments.
+hipError_t seq_state(const LaunchArgs &a, const SeqArgs &k, bool both, unsigned grid, hipStream_t s) {
+    return a.bf16 ? seq16_state(a.dstate, k, both, grid, s) : run_state_f32(a.dstate, k, both, grid, s);
+}
+hipError_t seq_out(const LaunchArgs &a, const SeqArgs &k, bool rev, unsigned grid, hipStream_t s) {
+    if (!a.bf16) return run_out<true>(a.dstate, k, rev, grid, s);
+    if (!rev && !k.emit && k.y && seq16_pairs(k, grid)) return seq16_out(a.dstate, k, SeqOut::kFwd, grid, s);
+    return run_out<false>(a.dstate, k, rev, grid, s);
+}
+// Both branches of one input set, k and rev the states entering every segment in their
+// directions (skips D and D_rev).  bf16 forms each chunk's decay-weighted C.B^T once, for both.
+hipError_t seq_out_both(const LaunchArgs &a, SeqArgs k, const SeqArgs &rev, unsigned grid, hipStream_t s) {
+    if (!a.bf16) {
+        const hipError_t e = run_out<true>(a.dstate, k, false, grid, s);
+        return e != hipSuccess ? e : run_out<true>(a.dstate, rev, true, grid, s);
+    }
+    k.skip2 = rev.skip;
+    const hipError_t e = seq16_out(a.dstate, k, SeqOut::kBoth, grid, s);
+    return e != hipSuccess ? e : seq16_out(a.dstate, rev, SeqOut::kPre, grid, s);
+}
+// Whether (row, head) pairs walk the whole sequence in one segment each, which spares the pass
+// for the states entering the segments (a third of the outputs' time) and the combination, but
+// leaves the chip to `units` workgroups.  A CU runs two of them (one at dstate 128 in fp32); a
+// last round of at most half the slots takes 0.6 of a full one.  Measured with outputs and
+// normalisation, one segment against several: 256 pairs of 8,192 tokens 666 us against 686,
+// 512 of 16,384 2,266 against 2,642, 640 of 4,096 785 against 857, 4,096 of 1,024 1,147
+// against 1,402.
+bool one_segment(const LaunchArgs &a) {
+    const int64_t units = static_cast<int64_t>(a.batch) * a.nheads;
+    const int64_t slots = !a.bf16 && a.dstate == 128 ? 256 : 512;
+    const int64_t rest = units % slots;
+    const double rounds = units / slots + (rest == 0 ? 0. : (2 * rest <= slots ? 0.6 : 1.));
+    return 2 * units >= slots && rounds * slots <= 1.33 * units;
+}
+
 SeqArgs seq_args(const LaunchArgs &a, int64_t T, const SeqPlan &pl, void *ws) {
     SeqArgs k;
     k.x = a.x;
@@ -1088,6 +1099,7 @@ SeqArgs seq_args(const LaunchArgs &a, int64_t T, const SeqPlan &pl, void *ws) {
     k.Cm = a.Cm;
     k.A = a.A;
     k.skip = a.D;
+    k.skip2 = nullptr;
     k.y = a.y;
     k.ws = static_cast<float *>(ws);
     k.tot = ws ? static_cast<float *>(ws) + pl.state_bytes / 4 : nullptr;
@@ -1120,6 +1132,17 @@ SeqArgs seq_args(const LaunchArgs &a, int64_t T, const SeqPlan &pl, void *ws) {
     return k;
 }
 
+// T tokens as one segment per row and head (no workspace).
+SeqArgs one_segment_args(const LaunchArgs &a, int64_t T) {
+    SeqPlan pl;
+    pl.seg_len = T;
+    pl.nseg = 1;
+    pl.dirs = 1;
+    pl.state_bytes = 0;
+    pl.total_bytes = 0;
+    return seq_args(a, T, pl, nullptr);
+}
+
 hipError_t combine(const LaunchArgs &a, const SeqPlan &pl, const SeqArgs &k, float *pool,
                    bool write_final, hipStream_t s) {
     CombineArgs c;
@@ -1150,44 +1173,39 @@ int launch_full_window(const LaunchArgs &a, int64_t T, void *ws, void *stream) {
     const SeqPlan pl = seq_plan(a.batch, a.nheads, a.dstate, T, 2);
     SeqArgs k = seq_args(a, T, pl, pl.nseg > 1 ? ws : nullptr);
     const unsigned grid = static_cast<unsigned>(static_cast<int64_t>(a.batch) * a.nheads * pl.nseg);
-    const bool f32 = !a.bf16;
     if (pl.nseg > 1) {
         // local states, then the states entering every segment
-        if ((f32 ? run_state<true>(a.dstate, k, true, grid, s)
-                 : run_state<false>(a.dstate, k, true, grid, s)) != hipSuccess)
-            return BDLM_E_LAUNCH;
+        if (seq_state(a, k, true, grid, s) != hipSuccess) return BDLM_E_LAUNCH;
         if (combine(a, pl, k, nullptr, false, s) != hipSuccess) return BDLM_E_LAUNCH;
         k.zero_init = 0;
     }
     k.skip = a.D;
-    if ((f32 ? run_out<true>(a.dstate, k, false, grid, s) : run_out<false>(a.dstate, k, false, grid, s)) !=
-        hipSuccess)
-        return BDLM_E_LAUNCH;
-    k.skip = a.D_rev;
-    if ((f32 ? run_out<true>(a.dstate, k, true, grid, s) : run_out<false>(a.dstate, k, true, grid, s)) !=
-        hipSuccess)
-        return BDLM_E_LAUNCH;
-    return BDLM_OK;
+    SeqArgs r = k;
+    r.skip = a.D_rev;
+    return seq_out_both(a, k, r, grid, s) == hipSuccess ? BDLM_OK : BDLM_E_LAUNCH;
 }
 
 int launch_prefill(const LaunchArgs &a, int64_t T, void *ws, void *stream, const SeqPlan *plan) {
     if (a.batch == 0 || T == 0) return BDLM_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const SeqPlan pl = plan ? *plan : seq_plan(a.batch, a.nheads, a.dstate, T, 1);
+    if (pl.nseg == 1 || (a.y && one_segment(a))) {
+        // one segment per row and head: from the cached state and back to it in one launch
+        SeqArgs k = one_segment_args(a, T);
+        k.pool_in = a.h_pool;
+        k.pool_out = a.h_pool;
+        const unsigned g1 = static_cast<unsigned>(static_cast<int64_t>(a.batch) * a.nheads);
+        return seq_out(a, k, false, g1, s) == hipSuccess ? BDLM_OK : BDLM_E_LAUNCH;
+    }
     SeqArgs k = seq_args(a, T, pl, ws);
     const unsigned grid = static_cast<unsigned>(static_cast<int64_t>(a.batch) * a.nheads * pl.nseg);
-    const bool f32 = !a.bf16;
-    if ((f32 ? run_state<true>(a.dstate, k, false, grid, s)
-             : run_state<false>(a.dstate, k, false, grid, s)) != hipSuccess)
-        return BDLM_E_LAUNCH;
+    if (seq_state(a, k, false, grid, s) != hipSuccess) return BDLM_E_LAUNCH;
     // the cached states enter segment 0; the final states go back to the cache
     if (combine(a, pl, k, a.h_pool, true, s) != hipSuccess) return BDLM_E_LAUNCH;
     if (a.y) {
         k.zero_init = 0;
         k.skip = a.D;
-        if ((f32 ? run_out<true>(a.dstate, k, false, grid, s)
-                 : run_out<false>(a.dstate, k, false, grid, s)) != hipSuccess)
-            return BDLM_E_LAUNCH;
+        if (seq_out(a, k, false, grid, s) != hipSuccess) return BDLM_E_LAUNCH;
     }
     return BDLM_OK;
 }
@@ -1199,7 +1217,12 @@ int launch_boundary_states(const LaunchArgs &a, int64_t nblocks, const float *s_
     // segments of G whole blocks: local segment states (seg_state), the states entering
     // the segments (seg_combine), then one sweep per segment, a block per chunk, that
     // writes every block's entering state (and the forward outputs if wanted)
-    const BoundaryPlan bp = boundary_plan(a.batch, a.nheads, a.dstate, nblocks, a.L);
+    BoundaryPlan bp = boundary_plan(a.batch, a.nheads, a.dstate, nblocks, a.L);
+    if (one_segment(a)) {
+        bp.blocks_per_seg = nblocks;
+        bp.nseg = 1;
+        bp.state_bytes = 0;
+    }
     SeqPlan pl;
     pl.seg_len = bp.blocks_per_seg * a.L;
     pl.nseg = bp.nseg;
@@ -1208,11 +1231,8 @@ int launch_boundary_states(const LaunchArgs &a, int64_t nblocks, const float *s_
     pl.total_bytes = bp.total_bytes;
     SeqArgs k = seq_args(a, nblocks * a.L, pl, bp.nseg > 1 ? ws : nullptr);
     const unsigned grid = static_cast<unsigned>(static_cast<int64_t>(a.batch) * a.nheads * bp.nseg);
-    const bool f32 = !a.bf16;
     if (bp.nseg > 1 || s_init) {
-        if (bp.nseg > 1 && (f32 ? run_state<true>(a.dstate, k, false, grid, s)
-                                : run_state<false>(a.dstate, k, false, grid, s)) != hipSuccess)
-            return BDLM_E_LAUNCH;
+        if (bp.nseg > 1 && seq_state(a, k, false, grid, s) != hipSuccess) return BDLM_E_LAUNCH;
         if (bp.nseg == 1) {   // one segment: its entering state is s_init itself
             k.pool_in = s_init;
             k.use_slots = 0;
@@ -1222,31 +1242,20 @@ int launch_boundary_states(const LaunchArgs &a, int64_t nblocks, const float *s_
             k.zero_init = 0;
         }
     }
+    if (!a.y) k.Cm = a.Bm;   // C is not needed (and may be null): the sweep stages B in its place
     k.emit = s_out;
     k.emit_blocks = nblocks;
     k.skip = a.D;
     hipError_t e;
     if (a.L == 16 || a.L == 32) {   // 64-token chunks carrying the state block by block
         k.cstride = kC;
-        e = f32 ? run_out_sub<true>(a.dstate, k, a.L, grid, s)
-                : run_out_sub<false>(a.dstate, k, a.L, grid, s);
+        e = a.bf16 ? run_out_sub<false>(a.dstate, k, a.L, grid, s) : run_out_sub<true>(a.dstate, k, a.L, grid, s);
     } else {                        // one block per chunk
         k.cstride = a.L;
-        e = f32 ? run_out<true>(a.dstate, k, false, grid, s) : run_out<false>(a.dstate, k, false, grid, s);
+        e = seq_out(a, k, false, grid, s);
     }
     if (e != hipSuccess) return BDLM_E_LAUNCH;
     return BDLM_OK;
-}
-
-// One segment per row: a block of any length from the cached state.
-static SeqArgs block_args(const LaunchArgs &a) {
-    SeqPlan pl;
-    pl.seg_len = a.L;
-    pl.nseg = 1;
-    pl.dirs = 1;
-    pl.state_bytes = 0;
-    pl.total_bytes = 0;
-    return seq_args(a, a.L, pl, nullptr);
 }
 
 int launch_block_long(const LaunchArgs &fwd, const LaunchArgs &rev, bool commit, bool want_y,
@@ -1254,27 +1263,25 @@ int launch_block_long(const LaunchArgs &fwd, const LaunchArgs &rev, bool commit,
     if (fwd.batch == 0 || fwd.L == 0) return BDLM_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const unsigned grid = static_cast<unsigned>(static_cast<int64_t>(fwd.batch) * fwd.nheads);
-    const bool f32 = !fwd.bf16;
     // forward from the cached state (a commit writes the final state back in place)
-    SeqArgs k = block_args(fwd);
+    SeqArgs k = one_segment_args(fwd, fwd.L);
     k.pool_in = fwd.h_pool;
     k.pool_out = commit ? fwd.h_pool : nullptr;
     k.y = want_y ? fwd.y : nullptr;
     k.skip = fwd.D;
-    if (k.y || k.pool_out) {
-        if ((f32 ? run_out<true>(fwd.dstate, k, false, grid, s)
-                 : run_out<false>(fwd.dstate, k, false, grid, s)) != hipSuccess)
-            return BDLM_E_LAUNCH;
-    }
-    if (!want_y) return BDLM_OK;
     // reverse inside the block from zero, added onto y
-    SeqArgs r = block_args(rev);
+    SeqArgs r = one_segment_args(rev, rev.L);
     r.y = fwd.y;
     r.skip = rev.D_rev;
-    if ((f32 ? run_out<true>(rev.dstate, r, true, grid, s)
-             : run_out<false>(rev.dstate, r, true, grid, s)) != hipSuccess)
-        return BDLM_E_LAUNCH;
-    return BDLM_OK;
+    const bool shared = fwd.x == rev.x && fwd.dt == rev.dt && fwd.Bm == rev.Bm && fwd.Cm == rev.Cm && fwd.A == rev.A;
+    hipError_t e = hipSuccess;
+    if (want_y && shared) {
+        e = seq_out_both(fwd, k, r, grid, s);
+    } else {
+        if (k.y || k.pool_out) e = seq_out(fwd, k, false, grid, s);
+        if (e == hipSuccess && want_y) e = seq_out(rev, r, true, grid, s);
+    }
+    return e == hipSuccess ? BDLM_OK : BDLM_E_LAUNCH;
 }
 
 }  // namespace bdlm
