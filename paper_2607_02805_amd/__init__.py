@@ -29,6 +29,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libbdlm.so")
+BIND_PATH = os.path.join(_HERE, "_bind.so")
 HEADER_PATH = os.path.join(os.path.dirname(_HERE), "include", "bdlm.h")
 
 HEADDIM = 64
@@ -149,6 +150,31 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_marshal = None
+
+
+def _native():
+    """The native marshalling (csrc/bdlm_bind.cpp): functions named as those here, which take
+    the plain case of a call and answer NotImplemented to every other."""
+    global _marshal
+    if _marshal is None:
+        lib()
+        _torch()
+        if not os.path.exists(BIND_PATH):
+            raise RuntimeError(f"{BIND_PATH} is missing: build it with "
+                               "`python -m paper_2607_02805_amd.build`")
+        from . import _bind
+        _marshal = _bind
+    return _marshal
+
+
+def _answer(got, where: str):
+    """The result of a native call that was not NotImplemented: an int is a failure's status."""
+    if type(got) is int:
+        raise BdlmError(got, where)
+    return got
+
+
 def strerror(code: int) -> str:
     return lib().bdlm_strerror(int(code)).decode()
 
@@ -266,6 +292,9 @@ def scan_block_step(x, dt, A, B, C, D, D_rev, h_pool, y=None, slot_idx=None, str
     ``h_pool`` is read only; ``slot_idx`` (host ints, optional) maps batch rows to
     cache slots.  Work is enqueued on ``stream`` (default: torch's current stream).
     """
+    got = _native().scan_block_step(x, dt, A, B, C, D, D_rev, h_pool, y, slot_idx, stream)
+    if got is not NotImplemented:
+        return _answer(got, "bdlm_scan_block_step")
     torch = _torch()
     d = _desc(x, dt, B, C)
     H, N = d.nheads, d.dstate
@@ -286,9 +315,13 @@ def scan_block_step_sep(fwd, rev, h_pool, y=None, slot_idx=None, stream=None):
     (x, dt, A, B, C, skip) tuples of the same shapes and strides; the forward branch
     continues the cached state with skip ``fwd[5]`` (D), the reverse branch runs inside
     the block from zero with skip ``rev[5]`` (D_rev).  Returns y (float32 [B, L, H, 64])."""
-    torch = _torch()
     x, dt, A, B, C, D = fwd
     xr, dtr, Ar, Br, Cr, Dr = rev
+    got = _native().scan_block_step_sep(x, dt, A, B, C, D, xr, dtr, Ar, Br, Cr, Dr, h_pool, y,
+                                        slot_idx, stream)
+    if got is not NotImplemented:
+        return _answer(got, "bdlm_scan_block_step_sep")
+    torch = _torch()
     for a, b, what in ((x, xr, "x"), (dt, dtr, "dt"), (A, Ar, "A"), (B, Br, "B"), (C, Cr, "C"),
                        (D, Dr, "D")):
         if tuple(a.shape) != tuple(b.shape) or a.dtype != b.dtype:
@@ -338,6 +371,10 @@ def conv_block_step(x, dt, A, B, C, D, D_rev, conv_w, conv_b, conv_pool, h_pool,
     """A denoising step with the mixer's convolution: x, B, C are pre-convolution inputs;
     the forward branch's convolution continues from ``conv_pool`` (read only), the
     reverse branch's is zero-padded inside the block.  Returns y (float32 [B, L, H, 64])."""
+    got = _native().conv_block_step(x, dt, A, B, C, D, D_rev, conv_w, conv_b, conv_pool,
+                                    h_pool, y, slot_idx, stream, workspace)
+    if got is not NotImplemented:
+        return _answer(got, "bdlm_conv_block_step")
     torch = _torch()
     d = _desc(x, dt, B, C)
     H, N = d.nheads, d.dstate
@@ -362,6 +399,11 @@ def conv_commit_boundary(x, dt, A, B, C, D, D_rev, conv_w, conv_b, conv_pool, h_
                          stream=None, workspace=None):
     """Commit with the mixer's convolution: the SSM states advance over the forward
     branch's convolved block and ``conv_pool`` keeps the last three pre-convolution rows."""
+    got = _native().conv_commit_boundary(x, dt, A, B, C, D, D_rev, conv_w, conv_b, conv_pool,
+                                         h_pool, n_committed, n_blocks, expected_block_index,
+                                         slot_idx, y_clean, stream, workspace)
+    if got is not NotImplemented:
+        return _answer(got, "bdlm_conv_commit_boundary")
     torch = _torch()
     d = _desc(x, dt, B, C)
     H, N = d.nheads, d.dstate
@@ -397,6 +439,10 @@ def commit_boundary(x, dt, A, B, C, D, D_rev, h_pool, n_committed, n_blocks,
     place.  ``y_clean``: None (skip), True (allocate and return) or a float32 tensor.
     Returns ``y_clean`` (or None).
     """
+    got = _native().commit_boundary(x, dt, A, B, C, D, D_rev, h_pool, n_committed, n_blocks,
+                                    expected_block_index, slot_idx, y_clean, stream)
+    if got is not NotImplemented:
+        return _answer(got, "bdlm_commit_boundary")
     torch = _torch()
     d = _desc(x, dt, B, C)
     H, N = d.nheads, d.dstate
@@ -431,6 +477,10 @@ def commit_step(clean, nxt, A, D, D_rev, h_pool, n_committed, n_blocks, expected
     state once.  Returns (y_next, y_clean)."""
     x, dt, B, C = clean
     xn, dtn, Bn, Cn = nxt
+    got = _native().commit_step(x, dt, B, C, xn, dtn, Bn, Cn, A, D, D_rev, h_pool, n_committed,
+                                n_blocks, expected_block_index, slot_idx, y_clean, y_next, stream)
+    if got is not NotImplemented:
+        return _answer(got, "bdlm_commit_step")
     for a, b, what in ((x, xn, "x"), (dt, dtn, "dt"), (B, Bn, "B"), (C, Cn, "C")):
         if tuple(a.shape) != tuple(b.shape) or a.dtype != b.dtype or a.stride() != b.stride():
             raise ValueError(f"clean and next {what} must share shape, dtype and strides")
@@ -500,6 +550,9 @@ def scan_full_window(x, dt, A, B, C, D, D_rev, y=None, stream=None, workspace=No
     zero plus reverse over the whole window from zero.  x is [B, W, H, 64]; returns y
     (float32 [B, W, H, 64]).  ``workspace``: a device tensor of at least
     :func:`full_window_workspace_bytes` bytes, 256-byte aligned (default: allocated)."""
+    got = _native().scan_full_window(x, dt, A, B, C, D, D_rev, y, stream, workspace)
+    if got is not NotImplemented:
+        return _answer(got, "bdlm_scan_full_window")
     torch = _torch()
     d = _desc(x, dt, B, C)
     H = d.nheads
@@ -522,6 +575,11 @@ def prefill(x, dt, A, B, C, D, h_pool, n_committed, n_blocks, expected_block_ind
     Bookkeeping advances by T tokens and ``blocks_in_prefix`` blocks.  ``y_fwd``: None,
     True (allocate and return) or a float32 tensor for the forward outputs.
     ``workspace``: as for :func:`scan_full_window` (:func:`prefill_workspace_bytes`)."""
+    got = _native().prefill(x, dt, A, B, C, D, h_pool, n_committed, n_blocks,
+                            expected_block_index, blocks_in_prefix, slot_idx, y_fwd, stream,
+                            workspace)
+    if got is not NotImplemented:
+        return _answer(got, "bdlm_prefill")
     torch = _torch()
     d = _desc(x, dt, B, C)
     H, N = d.nheads, d.dstate
@@ -555,6 +613,11 @@ def prefill_noalloc(x, dt, A, B, C, D, h_pool, n_committed, n_blocks, expected_b
     graph capture or a loop that must not allocate.  The segment states use the device
     scratch the library owns (``SCRATCH_BYTES`` per device); calls that overlap on one
     device race."""
+    got = _native().prefill_noalloc(x, dt, A, B, C, D, h_pool, n_committed, n_blocks,
+                                    expected_block_index, blocks_in_prefix, slot_idx, y_fwd,
+                                    stream)
+    if got is not NotImplemented:
+        return _answer(got, "bdlm_prefill_noalloc")
     d = _desc(x, dt, B, C)
     H, N = d.nheads, d.dstate
     nslots = h_pool.shape[0]
@@ -654,6 +717,9 @@ def gated_rmsnorm(y, z, norm_w, eps=1e-5, ngroups=1, out=None, stream=None):
     [B, L, H * 64] with unit channel stride (a slice of a projection output is fine);
     ``norm_w`` float32 [H * 64].  ``out`` may be ``y`` (in place).  Returns ``out``.
     """
+    got = _native().gated_rmsnorm(y, z, norm_w, eps, ngroups, out, stream)
+    if got is not NotImplemented:
+        return _answer(got, "bdlm_gated_rmsnorm")
     torch = _torch()
     if y.dtype != torch.float32 or not y.is_contiguous() or y.dim() not in (3, 4):
         raise ValueError("y must be a contiguous float32 [B, L, H, 64] or [B, L, H*64] tensor")

@@ -1,4 +1,5 @@
-"""Build libbdlm.so in-tree: HIP kernels for gfx950 with hipcc, the C ABI with g++.
+"""Build in-tree: libbdlm.so (HIP kernels for gfx950 with hipcc, the C ABI with g++) and
+_bind.so, which marshals torch tensors into it.
 
 Usage: ``python -m paper_2607_02805_amd.build``.  Always recompiles.
 """
@@ -7,6 +8,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -15,6 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbdlm.so")
+BIND = os.path.join(HERE, "_bind.so")
 PROBE_LIB = os.path.join(HERE, "libbdlm_probe.so")
 
 ARCH = "gfx950"
@@ -42,6 +45,20 @@ HIP_SRCS = ("bdlm_scan.hip", "bdlm_seq.hip", "bdlm_seq16.hip", "bdlm_mask.hip", 
             "bdlm_mix.hip", "bdlm_norm.hip", "bdlm_scratch.hip")
 
 
+def _bind_cmd(out: str) -> list[str]:
+    import torch
+    base = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-DUSE_ROCM",
+            "-D__HIP_PLATFORM_AMD__", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+            "-isystem", os.path.join(base, "include"),
+            "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+            "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"),
+            f"-I{INCLUDE}", os.path.join(CSRC, "bdlm_bind.cpp"), "-o", out,
+            f"-L{os.path.join(base, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10",
+            f"-L{HERE}", "-l:libbdlm.so", "-Wl,-rpath,$ORIGIN"]
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     cmds, objs = [], []
@@ -60,6 +77,9 @@ def build(verbose: bool = False) -> str:
     tmp = LIB + ".tmp"
     _run([HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp, *objs, a_obj])
     os.replace(tmp, LIB)
+    btmp = BIND + ".tmp"
+    _run(_bind_cmd(btmp))
+    os.replace(btmp, BIND)
     # the benchmark's streaming probe: a library of its own, outside the product ABI
     ptmp = PROBE_LIB + ".tmp"
     _run([HIPCC, *HIP_FLAGS, "-shared", "-o", ptmp, os.path.join(CSRC, "bdlm_probe.hip")])
