@@ -41,9 +41,10 @@ CSRC = os.path.join(ROOT, "paper_2607_02805_amd", "csrc")
 # records their hash; a figure is read back only while the hash still matches)
 SOURCE_SETS = {
     "block": ("bdlm_scan.hip", "bdlm_device.h"),
-    "seq": ("bdlm_seq.hip", "bdlm_seq16.hip", "bdlm_seq.h", "bdlm_device.h"),
-    "all": ("bdlm_scan.hip", "bdlm_seq.hip", "bdlm_seq16.hip", "bdlm_seq.h", "bdlm_mask.hip",
-            "bdlm_conv.hip", "bdlm_mix.hip", "bdlm_norm.hip", "bdlm_device.h", "bdlm_launch.h"),
+    "seq": ("bdlm_seq.hip", "bdlm_seq16.hip", "bdlm_seq.h", "bdlm_images.h", "bdlm_device.h"),
+    "all": ("bdlm_scan.hip", "bdlm_seq.hip", "bdlm_seq16.hip", "bdlm_seq.h", "bdlm_mask.hip", "bdlm_maskw.hip",
+            "bdlm_conv.hip", "bdlm_mix.hip", "bdlm_norm.hip", "bdlm_images.h", "bdlm_device.h",
+            "bdlm_launch.h"),
 }
 KERNEL_SRCS = [os.path.join(CSRC, f) for f in SOURCE_SETS["block"]]
 PROFILES = os.path.join(ROOT, "profiles")

@@ -41,7 +41,8 @@ def _run(cmd: list[str]) -> None:
             sys.stderr.write(line + "\n")
 
 
-HIP_SRCS = ("bdlm_scan.hip", "bdlm_seq.hip", "bdlm_seq16.hip", "bdlm_mask.hip", "bdlm_conv.hip",
+HIP_SRCS = ("bdlm_scan.hip", "bdlm_seq.hip", "bdlm_seq16.hip", "bdlm_mask.hip", "bdlm_maskw.hip",
+            "bdlm_conv.hip",
             "bdlm_mix.hip", "bdlm_norm.hip", "bdlm_scratch.hip")
 
 

@@ -408,7 +408,7 @@ int bdlm_scan_block_step_sep(const bdlm_desc_t *d, const void *x, const void *dt
         const int64_t r0 = fc.slots ? fc.slots - f.slots : 0;
         const bdlm::LaunchArgs rc = rows_of(r, r0, fc.batch, yr);
         return d->block_len <= BDLM_MAX_BLOCK_LEN ? bdlm::launch_block_pair(fc, rc, false, true, stream)
-                                                  : bdlm::launch_block_long(fc, rc, false, true, stream);
+                                                  : bdlm::launch_block_long_sep(fc, rc, stream);
     });
 }
 

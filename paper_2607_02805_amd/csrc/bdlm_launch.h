@@ -188,9 +188,15 @@ int launch_block_long(const LaunchArgs &fwd, const LaunchArgs &rev, bool commit,
 // one launch in masked-matrix form, one workgroup per (row, head) (bdlm_mask.hip).
 bool long_masked_fits(const LaunchArgs &a);
 int launch_long_masked(const LaunchArgs &a, bool commit, bool want_y, void *stream);
+// The same in source windows, two workgroups per CU, where that is faster (bdlm_maskw.hip).
+bool masked_windows_fit(const LaunchArgs &a);
+int launch_masked_windows(const LaunchArgs &a, bool commit, bool want_y, void *stream);
 // A long block's step or commit with one input set: launch_long_masked where it fits,
 // else launch_block_long.
 int launch_block_long_shared(const LaunchArgs &a, bool commit, bool want_y, void *stream);
+// A long block's step whose reverse branch has its own inputs (of fwd's shapes and strides):
+// the masked form, in one launch, where it fits, else launch_block_long.
+int launch_block_long_sep(const LaunchArgs &fwd, const LaunchArgs &rev, void *stream);
 
 // The convolution part of the boundary state, then the block step (commit: the
 // commit) on the convolved inputs: a.x / a.Bm / a.Cm are the pre-convolution inputs,

@@ -581,6 +581,7 @@ int launch_long_masked(const LaunchArgs &a, bool commit, bool want_y, void *stre
     if (a.batch == 0 || a.L == 0) return BDLM_OK;
     if (!long_masked_fits(a)) return BDLM_E_SHAPE;
     if (!commit && !want_y) return BDLM_OK;
+    if (masked_windows_fit(a)) return launch_masked_windows(a, commit, want_y, stream);
     MaskArgs k;
     k.x = a.x;
     k.dt = a.dt;

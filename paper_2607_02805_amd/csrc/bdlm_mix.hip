@@ -41,6 +41,7 @@
 
 #include "bdlm.h"
 #include "bdlm_device.h"
+#include "bdlm_images.h"
 #include "bdlm_launch.h"
 
 namespace bdlm {
@@ -332,23 +333,6 @@ template <int NW> struct XImg {
     }
 };
 constexpr float kLeast = -60.f;                        // log2 of the least source weight
-
-// Inclusive sum of doubles over the wave (wave_inclusive_sum's steps on both halves).
-template <int CTRL, int ROW_MASK, bool BOUND_ZERO>
-__device__ __forceinline__ double dpp_d(double v) {
-    const int2 u = __builtin_bit_cast(int2, v);
-    return __builtin_bit_cast(double, int2{__builtin_amdgcn_update_dpp(0, u.x, CTRL, ROW_MASK, 0xf, BOUND_ZERO),
-                                           __builtin_amdgcn_update_dpp(0, u.y, CTRL, ROW_MASK, 0xf, BOUND_ZERO)});
-}
-__device__ __forceinline__ double wave_inclusive_sum_d(double v) {
-    v += dpp_d<0x111, 0xf, true>(v);
-    v += dpp_d<0x112, 0xf, true>(v);
-    v += dpp_d<0x114, 0xf, true>(v);
-    v += dpp_d<0x118, 0xf, true>(v);
-    v += dpp_d<0x142, 0xa, false>(v);
-    v += dpp_d<0x143, 0xc, false>(v);
-    return v;
-}
 
 template <int NW, int MR, int NS, bool BF16, bool COMMIT>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 8 ? 4 : 2)))

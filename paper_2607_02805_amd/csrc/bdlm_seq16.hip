@@ -30,6 +30,7 @@
 
 #include "bdlm.h"
 #include "bdlm_device.h"
+#include "bdlm_images.h"
 #include "bdlm_launch.h"
 #include "bdlm_seq.h"
 
@@ -41,11 +42,6 @@ constexpr int kThreads = 256;    // 4 waves
 constexpr int kFwd = 0, kBoth = 1, kPre = 2;
 
 __device__ __forceinline__ float ex2(float v) { return __builtin_amdgcn_exp2f(v); }
-__device__ __forceinline__ f32x4 quad_val(s16x4 v) {
-    return f32x4{bf16_to_f32(v[0]), bf16_to_f32(v[1]), bf16_to_f32(v[2]), bf16_to_f32(v[3])};
-}
-__device__ __forceinline__ s16x4 lo4(uint4 v) { return as_s16x4(uint2{v.x, v.y}); }
-__device__ __forceinline__ s16x4 hi4(uint4 v) { return as_s16x4(uint2{v.z, v.w}); }
 
 // Decode the workgroup into (batch row, segment, head): consecutive units of one
 // (row, segment) share B and C, so they are kept on one XCD.
@@ -77,36 +73,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_n(const void *base, int b
 }
 constexpr int kNT = 2;   // buffer cache policy: nontemporal
 
-// Row images, permuted so that every access pattern meets distinct banks.  C: 16-byte piece c of
-// token t (staging writes whole rows, operand reads 16 tokens by one piece).
-template <int NS>
-__device__ __forceinline__ int c_at(int t, int c) {
-    if constexpr (NS == 128) return t * 16 + (c ^ (4 * (t & 3) + ((t >> 2) & 3)));
-    else if constexpr (NS == 64) return t * 8 + (c ^ (4 * ((t >> 1) & 1) + ((t >> 2) & 3)));
-    else if constexpr (NS == 32) return t * 4 + (c ^ ((t >> 2) & 3));
-    else return t * 2 + (c ^ ((t >> 3) & 1));
-}
-// B: 8-byte quad (state tile q, lane group a) of token t.  The four quads of a tile lie side by
+// B image: 8-byte quad (state tile q, lane group a) of token t.  The four quads of a tile lie side by
 // side (a transpose read takes them from four tokens at once), whatever dstate they hold.
 template <int NS>
 __device__ __forceinline__ int b_at(int t, int q, int a) {
     constexpr int QN = NS / 16;
     return t * (NS / 4) + ((q ^ ((t / (8 / QN)) & (QN - 1))) * 4) + (a ^ (2 * ((t >> 3) & 1)));
 }
-// x: 16-byte piece c of token t.
-__device__ __forceinline__ int x_at(int t, int c) { return t * 8 + (c ^ (2 * ((t >> 1) & 3)) ^ ((t >> 3) & 1)); }
-
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-// LDS transpose read (gfx950): every lane reads four bf16 at its own 8-byte-aligned
-// address, and within each group of 16 lanes, lane 4a + b receives element b of the words
-// read by lanes a, a + 4, a + 8 and a + 12 of its group, in that order.  So when lane s
-// of group kg reads the quad (token 4kg + s / 4, quad s % 4 of four column quads), lane (kg,
-// col) receives column col of tokens 4kg .. 4kg + 3.
-__device__ __forceinline__ s16x4 ds_read_tr(const uint2 *p) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(const_cast<uint2 *>(p)));
-}
-__device__ __forceinline__ int tr_tok(int lane) { return 4 * (lane >> 4) + ((lane & 15) >> 2); }
-
 // Dstate quad (of four) that tile q's rows 4 grp .. 4 grp + 3 hold, and the offset of those
 // values of column p in the pool layout.
 template <int NS>
@@ -193,12 +166,8 @@ struct Stager {
     }
 };
 
-// Operands over tokens.  x: lane (grp, col) gets tokens 16 jt + 4 grp .. +3 of column 16 wave +
-// col; B: the same tokens of the dstate index that row col of tile q holds.
-__device__ __forceinline__ s16x4 x_read(const uint4 *sX, int jt, int wave, int lane) {
-    const int a = lane & 3;
-    return ds_read_tr(reinterpret_cast<const uint2 *>(sX) + 2 * x_at(16 * jt + tr_tok(lane), 2 * wave + (a >> 1)) + (a & 1));
-}
+// B operand over tokens: lane (grp, col) gets tokens 16 jt + 4 grp .. +3 of the dstate index that
+// row col of tile q holds.
 template <int NS>
 __device__ __forceinline__ s16x4 bt_read(const uint2 *sB, int jt, int q, int lane) {
     return ds_read_tr(sB + b_at<NS>(16 * jt + tr_tok(lane), q, lane & 3));

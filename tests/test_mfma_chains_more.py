@@ -1,4 +1,4 @@
-"""The convolution-state kernels and the bf16 sequence kernels hand no MFMA accumulator from
+"""The convolution-state, bf16 sequence and windowed masked kernels hand no MFMA accumulator from
 one MFMA shape to another (the scan of test_mfma_chains.py on their sources)."""
 import os
 
@@ -8,7 +8,7 @@ from paper_2607_02805_amd import build
 from tests.test_mfma_chains import _compile_to_asm, mixed_shape_chains
 
 
-@pytest.mark.parametrize("src", ["bdlm_mix.hip", "bdlm_seq16.hip"])
+@pytest.mark.parametrize("src", ["bdlm_mix.hip", "bdlm_seq16.hip", "bdlm_maskw.hip"])
 def test_no_accumulator_crosses_mfma_shapes(src, tmp_path):
     if not os.path.exists(build.HIPCC):
         pytest.skip("hipcc not available")
