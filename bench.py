@@ -1210,21 +1210,22 @@ SEQ_WORKLOADS = """All workloads of `bench.py --sequence-only` (350M layer shape
 paper's 26, dstate 128, one group, bf16 activations unless stated):
 
 * full window: batch 4, 65,536 tokens, forward + reverse from zero; 16 segments of
-  4,096 tokens per row and head -- `seg_state` (both directions' local states, 2048
-  workgroups), `seg_combine` (1024 workgroups), `seg_out` forward and reverse (2048);
-* prefill: batch 16, 16,384 tokens -- `seg_state` (2048), `seg_combine` (2048);
-* all-block forward: batch 8, 8,192-token window, L = 32 (256 blocks; segments of 16
-  blocks) -- `seg_state` (4096), `seg_combine` (4096), `seg_out` with SUB = 32 carrying
-  the state block by block and writing the block states and the clean outputs (4096),
-  then the block step over 2,048 rows (65536 x 512);
+  4,096 tokens per row and head -- `seg_state16` (both directions' local states, 2048
+  workgroups), `seg_combine` (1024 workgroups), `seg_out16` with both triangles of each
+  chunk (mode 1, two heads per workgroup: 1024) and with the rest of the reverse branch
+  (mode 2: 2048);
+* prefill: batch 16, 16,384 tokens -- `seg_state16` (2048), `seg_combine` (2048);
+* all-block forward: batch 8, 8,192-token window, L = 32 (256 blocks in one segment) --
+  `seg_out` with SUB = 32 carrying the state block by block and writing the block states
+  and the clean outputs (256), then the block step over 2,048 rows (65536 x 512);
 * paper geometry: batch 16, 26 heads, L = 256 -- `bdlm_mask_block_kernel`, the block in
   masked-matrix form, one workgroup of eight waves per (row, head), each wave owning 32
   output tokens (416 workgroups of 512 threads);
 * separate reverse inputs: batch 16, L = 32 -- one block-kernel launch with both input
   sets (direction 3), 512 x 512;
 * convolution state: batch 16, L = 32 -- the fp32 block kernel with the convolution in
-  its staging (last template flag true), forward (direction 1; the commit instantiation
-  on commits) then reverse (direction 2), and `bdlm_conv_keep_kernel` on commits;
+  its staging (last template flag true), both branches (direction 3; the commit
+  instantiation on commits), and `bdlm_conv_keep_kernel` on commits;
 * gated RMS normalisation: 512 tokens x 2,048 channels -- `bdlm_gated_rmsnorm_kernel`
   alone and after the block step;
 * fused commit + next step: batch 16, L = 32 -- the block kernel's direction 4.

@@ -14,7 +14,7 @@ Entry points (same names as the C ABI):
   replaces the cached one (Sec. 4, Eq. boundary-state).
 * :func:`scan_full_window` -- the full-sequence bidirectional scan with no cache
   (the DiffuMamba-style contrast).
-* :func:`prefill` -- summarise a long clean prefix into the cached states in one launch.
+* :func:`prefill` -- summarise a long clean prefix into the cached states in one call.
 * :func:`cache_reset` -- empty the given cache slots.
 
 :class:`Cache` bundles a state pool with its host-side bookkeeping.
