@@ -185,7 +185,8 @@ int launch_block_long(const LaunchArgs &fwd, const LaunchArgs &rev, bool commit,
                       void *stream);
 
 // Blocks of 65 to 256 tokens with bf16 activations and one input set for both branches:
-// one launch in masked-matrix form, one workgroup per (row, head) (bdlm_mask.hip).
+// one launch in masked-matrix form, one workgroup per (row, head) (bdlm_mask.hip), where the
+// block's rows lie within 2 GiB of its first.
 bool long_masked_fits(const LaunchArgs &a);
 int launch_long_masked(const LaunchArgs &a, bool commit, bool want_y, void *stream);
 // The same in source windows, two workgroups per CU, where that is faster (bdlm_maskw.hip).

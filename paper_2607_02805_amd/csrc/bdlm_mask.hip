@@ -567,9 +567,15 @@ hipError_t mask_mt(const MaskArgs &k, int L, bool commit, unsigned grid, hipStre
 
 }  // namespace
 
+// (A workgroup addresses its whole block from one base, with 31-bit byte offsets: calls with
+// larger strides take the sequence kernels, which have a 64-bit base per 64 tokens.)
 bool long_masked_fits(const LaunchArgs &a) {
+    const int64_t last = a.L - 1;
+    auto in_range = [&](int64_t row, int64_t bytes) { return last * row + bytes <= 0x7fffffff; };
     return a.bf16 && a.L > 64 && a.L <= 256 && a.batch <= BDLM_MAX_SLOT_ROWS &&
-           (a.dstate == 16 || a.dstate == 32 || a.dstate == 64 || a.dstate == 128);
+           (a.dstate == 16 || a.dstate == 32 || a.dstate == 64 || a.dstate == 128) &&
+           in_range(2 * a.xs_t, 2 * kP) && in_range(2 * a.bcs_t, 2 * a.dstate) && in_range(2 * a.dts_t, 2) &&
+           in_range(int64_t(4) * kP * a.nheads, 4 * kP);
 }
 
 int launch_block_long_shared(const LaunchArgs &a, bool commit, bool want_y, void *stream) {

@@ -294,3 +294,47 @@ def test_step_separate_with_shared_inputs_equals_step():
     torch.cuda.synchronize()
     ref = oracle.block_step(d, from_pool(pool).astype(np.float64))
     assert rel_err(y1, ref) <= REL_TOL and rel_err(y2, ref) <= REL_TOL
+
+
+@pytest.mark.parametrize("N", [16, 64, 128])
+@pytest.mark.parametrize("xbytes,bcbytes", [(17 << 19, 1 << 12), (1 << 12, 1 << 24), (1 << 23, 1 << 23)])
+def test_block_rows_beyond_two_gib(N, xbytes, bcbytes):
+    """256 tokens with token strides above 8 MiB (a sequence-major tensor or a slice of one):
+    the rows span more than 2 GiB.  8 MiB itself is the last stride within."""
+    import paper_2607_02805_amd as bd
+    B, H, L = 2, 2, 256
+    w = bi.Workload("t", B, H, 64, N, 1, L, 0, True, 1, 10900 + N)
+    fwd, rev = sep_inputs(w, 10950 + N)
+    pool = bi.random_state(w, B, 3, 0.5).astype(np.float64)
+    buf = torch.zeros(L * max(xbytes, bcbytes) // 2, dtype=torch.bfloat16, device=DEV)
+    at = 0
+
+    def spread(t, row):
+        """t [B, L, heads or groups, n] with `row` bytes between tokens, in buf."""
+        nonlocal at
+        n = t[:, 0].numel()
+        v = buf.as_strided(t.shape, (t[0, 0].numel(), row // 2, t.shape[3], 1), at)
+        v.copy_(t)
+        at += (n + 7) // 8 * 8
+        return v
+    # (in the order x, x, then B and C: rows of one stride never meet those of another below 4 KiB)
+    vf, vr = to_dev(fwd), to_dev(rev)
+    for v in (vf, vr):
+        v["x"] = spread(v["x"], xbytes) if xbytes > 1 << 16 else v["x"]
+    for v in (vf, vr):
+        for k in ("B", "C"):
+            v[k] = spread(v[k], bcbytes) if bcbytes > 1 << 16 else v[k]
+    say("rows beyond 2 GiB", dict(N=N, xbytes=xbytes, bcbytes=bcbytes))
+    y = bd.scan_block_step_sep((vf["x"], vf["dt"], vf["A"], vf["B"], vf["C"], vf["D"]),
+                               (vr["x"], vr["dt"], vr["A"], vr["B"], vr["C"], vr["D_rev"]), pool_dev(pool))
+    h = pool_dev(pool)
+    nc, nb = np.zeros(B, np.int64), np.zeros(B, np.int64)
+    yc = bd.commit_boundary(vf["x"], vf["dt"], vf["A"], vf["B"], vf["C"], vf["D"], vf["D_rev"], h, nc, nb,
+                            y_clean=True)
+    torch.cuda.synchronize()
+    _, yf, _ = oracle.block_step(fwd, pool, parts=True)
+    _, _, yr = oracle.block_step(rev, np.zeros_like(pool), parts=True)
+    assert rel_err(y, yf + yr) <= REL_TOL
+    y_ref, *_, s_ref = oracle.block_step(fwd, pool, parts=True, final_state=True)
+    assert rel_err(yc, y_ref) <= REL_TOL
+    assert rel_err(from_pool(h), s_ref) <= REL_TOL

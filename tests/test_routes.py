@@ -1,0 +1,80 @@
+"""The dispatch rules of libbdlm, asked of the built library on the CPU: a call is sent to a
+kernel only where that kernel can address every byte of it.
+
+The rules are C++ functions of the library; a shim compiled here against its internal header
+fills their argument structure.
+"""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+import paper_2607_02805_amd as bd
+
+SHIM = r"""
+#include "bdlm_launch.h"
+using namespace bdlm;
+static LaunchArgs args(const int64_t *v) {
+    LaunchArgs a = {};
+    a.batch = v[0]; a.nheads = v[1]; a.ngroups = v[2]; a.L = v[3]; a.dstate = v[4]; a.bf16 = v[5];
+    a.xs_t = v[6]; a.dts_t = v[7]; a.bcs_t = v[8];
+    return a;
+}
+extern "C" int masked(const int64_t *v) { return long_masked_fits(args(v)); }
+extern "C" int windows(const int64_t *v) { return masked_windows_fit(args(v)); }
+extern "C" int mix(const int64_t *v) { return mix_fits(args(v)); }
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    bd.lib()
+    d = tmp_path_factory.mktemp("routes")
+    src, so = d / "shim.cpp", d / "shim.so"
+    src.write_text(SHIM)
+    csrc = os.path.join(os.path.dirname(bd.LIB_PATH), "csrc")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", f"-I{csrc}",
+                    f"-I{os.path.dirname(bd.HEADER_PATH)}", str(src), "-o", str(so),
+                    f"-L{os.path.dirname(bd.LIB_PATH)}", "-l:libbdlm.so",
+                    f"-Wl,-rpath,{os.path.dirname(bd.LIB_PATH)}"], check=True)
+    lib = ctypes.CDLL(str(so))
+
+    def ask(rule, batch, H, G, L, N, bf16, xs_t=None, dts_t=None, bcs_t=None):
+        v = (ctypes.c_int64 * 9)(batch, H, G, L, N, bf16, xs_t or H * 64, dts_t or H, bcs_t or G * N)
+        return bool(getattr(lib, rule)(v))
+    return ask
+
+
+RANGE = 0x7fffffff          # bytes of the buffer resources that the block kernels load through
+
+
+def last_byte(H, L, N, es, xs_t, dts_t, bcs_t):
+    """The furthest byte of a block that a workgroup addresses from its (row, head)'s base."""
+    return max((L - 1) * xs_t * es + 64 * es, (L - 1) * bcs_t * es + N * es, (L - 1) * dts_t * es + es,
+               (L - 1) * H * 256 + 256)
+
+
+@pytest.mark.parametrize("L", [65, 96, 128, 129, 200, 256])
+@pytest.mark.parametrize("N", [16, 32, 64, 128])
+def test_masked_kernels_take_only_what_they_address(rules, L, N):
+    """Token strides up to 16 MiB are accepted; 256 of them span 4 GiB."""
+    r = random.Random(100 * L + N)
+    for _ in range(400):
+        st = [8 * r.randint(128, 1 << 20) for _ in range(3)]
+        if r.random() < 0.5:                              # about the limit
+            k = r.randrange(3)
+            st[k] = 8 * (((1 << 31) // (2 * L) + r.randint(-64, 64)) // 8)
+        H = r.choice([1, 4, 26, 300, 8192, 33000, 65536])
+        last = last_byte(H, L, N, 2, *st)
+        took = rules("masked", 1, H, 1, L, N, 1, *st)
+        assert took == (last <= RANGE)
+        assert not rules("windows", 1, H, 1, L, N, 1, *st) or took
+
+
+@pytest.mark.parametrize("L", [65, 128, 256])
+def test_masked_kernels_keep_the_strides_of_a_projection(rules, L):
+    for H, G, N in ((1, 1, 16), (32, 1, 128), (26, 2, 64), (128, 8, 128)):
+        row = 2 * H * 64 + 2 * G * N + H
+        assert rules("masked", 16, H, G, L, N, 1, row, row, row)
