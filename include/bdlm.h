@@ -85,7 +85,8 @@ enum bdlm_dtype { BDLM_DTYPE_F32 = 0, BDLM_DTYPE_BF16 = 1 };
  *   B, C [batch][block_len][ngroups][dstate]: bc_stride = {batch, token, group};
  *      dstate unit stride; B and C share strides.
  * Strides may describe views into a larger projection output (e.g. slices of a
- * Mamba-2 in_proj result).  bdlm_desc_init fills contiguous strides.
+ * Mamba-2 in_proj result); a token stride of 0 repeats one row.  bdlm_desc_init fills
+ * contiguous strides.
  */
 typedef struct bdlm_desc {
     int64_t batch;

@@ -229,14 +229,13 @@ struct Stager {
         const int64_t w = window(c);
         const int lim = valid(c);
         // Forward, the chunk's rows past the segment are its last ones: the resources end
-        // after the valid rows, so those rows load as zeros with no per-row test.  In
+        // with the last valid row, so those rows load as zeros with no per-row test (or, at
+        // token strides shorter than a row, as parts of valid rows: they meet dt = 0).  In
         // reverse they are the first rows of the window and get an out-of-range offset.
-        const __amdgpu_buffer_rsrc_t rB =
-            REV ? rsrc(Bg + w * bcrow) : rsrc_n(Bg + w * bcrow, static_cast<int>(lim * bcrow));
-        const __amdgpu_buffer_rsrc_t rC =
-            REV ? rsrc(Cg + w * bcrow) : rsrc_n(Cg + w * bcrow, static_cast<int>(lim * bcrow));
-        const __amdgpu_buffer_rsrc_t rX =
-            REV ? rsrc(xg + w * xrow) : rsrc_n(xg + w * xrow, static_cast<int>(lim * xrow));
+        const int bcn = static_cast<int>((lim - 1) * bcrow) + NS * ES, xn = static_cast<int>((lim - 1) * xrow) + kP * ES;
+        const __amdgpu_buffer_rsrc_t rB = REV ? rsrc(Bg + w * bcrow) : rsrc_n(Bg + w * bcrow, bcn);
+        const __amdgpu_buffer_rsrc_t rC = REV ? rsrc(Cg + w * bcrow) : rsrc_n(Cg + w * bcrow, bcn);
+        const __amdgpu_buffer_rsrc_t rX = REV ? rsrc(xg + w * xrow) : rsrc_n(xg + w * xrow, xn);
 #pragma unroll
         for (int k = 0; k < G::BPT; ++k) {
             const int task = tid + kThreads * k;
@@ -263,16 +262,20 @@ struct Stager {
             }
         }
         if (wave == 0) {
-            const __amdgpu_buffer_rsrc_t rD =
-                REV ? rsrc(dtg + w * dtrow) : rsrc_n(dtg + w * dtrow, static_cast<int>(lim * dtrow));
+            // (a token stride of 0 gives every row one offset: dt_value drops what lies past)
+            const __amdgpu_buffer_rsrc_t rD = REV ? rsrc(dtg + w * dtrow)
+                                                  : rsrc_n(dtg + w * dtrow, static_cast<int>((lim - 1) * dtrow) + ES);
             const uint32_t o = !REV || lane < lim ? odt : kOOB;
             if constexpr (F32) dtraw = __builtin_amdgcn_raw_buffer_load_b32(rD, o, 0, 0);
             else dtraw = __builtin_amdgcn_raw_buffer_load_b16(rD, o, 0, 0);
         }
     }
 
-    __device__ __forceinline__ float dt_value() const {
-        return F32 ? __uint_as_float(dtraw) : __uint_as_float(dtraw << 16);
+    // dt of this lane's local token of chunk c, 0 past the segment (by a lane mask: the lane
+    // number held in a register for it crosses steps of occupancy, 10 % at fp32, dstate 32)
+    __device__ __forceinline__ float dt_value(int c) const {
+        const float v = F32 ? __uint_as_float(dtraw) : __uint_as_float(dtraw << 16);
+        return REV || __builtin_amdgcn_inverse_ballot_w64(~0ull >> (kC - valid(c))) ? v : 0.f;
     }
 
     // Row image of B or C (operand over dstate) from one task's four token rows.
@@ -472,7 +475,7 @@ __global__ void __launch_bounds__(kThreads, 1) bdlm_seg_state_kernel(const SeqAr
     for (int c = 0; c < nch; ++c) {
         st.stage(tid, sBt, nullptr, sBt, sXt);
         if (wave == 0)
-            decay_sums<BOTH>(st.dt_value(), A2, lane, sDt, sCs, sEc, sWs, sWr);
+            decay_sums<BOTH>(st.dt_value(c), A2, lane, sDt, sCs, sEc, sWs, sWr);
         __syncthreads();
         if (c + 1 < nch) st.issue(c + 1, tid, wave, lane);
 
@@ -595,7 +598,7 @@ __global__ void __launch_bounds__(kThreads, F32 ? 1 : 2) bdlm_seg_out_kernel(con
     for (int c = 0; c < nch; ++c) {
         st.stage(tid, sB, sC, sBt, sXt);
         if (wave == 0)
-            decay_sums<false>(st.dt_value(), A2, lane, sDt, sCs, sEc, sWs, nullptr);
+            decay_sums<false>(st.dt_value(c), A2, lane, sDt, sCs, sEc, sWs, nullptr);
         __syncthreads();
         // the next chunk's loads (the reverse pass, which also holds the y values it adds
         // onto, requests them after the Gram tiles instead: fewer registers live across the

@@ -71,6 +71,7 @@ __device__ __forceinline__ int64_t state_slot(const SeqArgs &a, int b, int h, in
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_n(const void *base, int bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), static_cast<short>(0), bytes, 0x00020000);
 }
+constexpr uint32_t kOOB = 0x80000000u;   // offset past every resource
 constexpr int kNT = 2;   // buffer cache policy: nontemporal
 
 // B image: 8-byte quad (state tile q, lane group a) of token t.  The four quads of a tile lie side by
@@ -88,8 +89,9 @@ template <int NS>
 __device__ __forceinline__ int quad_off(int q, int grp, int p) { return (n4_of<NS>(q, grp) * kP + p) * 4; }
 
 // One chunk's global loads into registers and their staging into LDS.  Local token i is row
-// i of the chunk, or (REV) row 63 - i; rows past the segment load as zeros (dt = 0: decay 1, no
-// input), which changes nothing.
+// i of the chunk, or (REV) row 63 - i; rows past the segment have dt = 0 (decay 1, no input),
+// which changes nothing, and load as zeros (at token strides shorter than a row, 0 among them, as
+// parts of valid rows).
 template <int NS, int HPW, bool REV, bool LOADC>
 struct Stager {
     static constexpr int NT = kThreads * HPW;                          // threads
@@ -128,9 +130,10 @@ struct Stager {
     __device__ __forceinline__ void issue(int c, int tid, bool scan) {
         const int64_t w = window(c);
         const int lim = valid(c);
-        const __amdgpu_buffer_rsrc_t rB = rsrc_n(Bg + w * bcrow, static_cast<int>(lim * bcrow));
-        const __amdgpu_buffer_rsrc_t rC = rsrc_n(Cg + w * bcrow, static_cast<int>(lim * bcrow));
-        const __amdgpu_buffer_rsrc_t rX = rsrc_n(xg + w * xrow, static_cast<int>(lim * xrow));
+        const int bcn = static_cast<int>((lim - 1) * bcrow) + 2 * NS, xn = static_cast<int>((lim - 1) * xrow) + 2 * kP;
+        const __amdgpu_buffer_rsrc_t rB = rsrc_n(Bg + w * bcrow, bcn);
+        const __amdgpu_buffer_rsrc_t rC = rsrc_n(Cg + w * bcrow, bcn);
+        const __amdgpu_buffer_rsrc_t rX = rsrc_n(xg + w * xrow, xn);
         const int bs = static_cast<int>((REV ? -RS : RS) * bcrow), xs = static_cast<int>((REV ? -32 : 32) * xrow);
         // (rows are at most 16 MiB: a chunk's byte offsets fit in 31 bits)
         const uint32_t ob = row(tid / CH) * static_cast<uint32_t>(bcrow) + (tid % CH) * 16;
@@ -144,9 +147,12 @@ struct Stager {
         }
 #pragma unroll
         for (int k = 0; k < 2; ++k) rx[k] = __builtin_amdgcn_raw_buffer_load_b128(rX, ox + k * xs, 0, 0);
-        if (scan)
-            dtraw = __builtin_amdgcn_raw_buffer_load_b16(rsrc_n(dtg + w * dtrow, static_cast<int>(lim * dtrow)),
-                                                          row(tid & 63) * static_cast<uint32_t>(dtrow), 0, 0);
+        if (scan) {
+            // (a lane mask: a comparison would hold the lane number in a register)
+            const bool in = __builtin_amdgcn_inverse_ballot_w64(REV ? ~0ull << (kC - lim) : ~0ull >> (kC - lim));
+            const uint32_t o = in ? row(tid & 63) * static_cast<uint32_t>(dtrow) : kOOB;
+            dtraw = __builtin_amdgcn_raw_buffer_load_b16(rsrc_n(dtg + w * dtrow, 0x7fffffff), o, 0, 0);
+        }
     }
     __device__ __forceinline__ float dt_value() const { return __uint_as_float(dtraw << 16); }
     __device__ __forceinline__ void stage(int tid, uint2 *sB, uint4 *sC, uint4 *sX) const {
