@@ -72,13 +72,15 @@ typedef __attribute__((address_space(1))) const float g_f;
 __device__ __forceinline__ float ex2(float v) { return __builtin_amdgcn_exp2f(v); }
 
 // v / (1 + e^-v): the quotient of the hardware reciprocal is corrected by its remainder (a
-// rounding of the quotient, as a division gives).  The exponential's argument stops at 87,
-// where e^87 is still finite.
+// rounding of the quotient, as a division gives).  Past 88 either way, where e^-v or its
+// reciprocal leaves the range, it is v or 0 (infinities: +inf and NaN, as the division gives).
 __device__ __forceinline__ float silu(float v) {
-    const float d = 1.f + ex2(fmaxf(v, -87.f) * -kLog2e);
+    const float d = 1.f + ex2(v * -kLog2e);
     const float r = __builtin_amdgcn_rcpf(d);
     const float q = v * r;
-    return fmaf(fmaf(-d, q, v), r, q);
+    // (both formed, then one selected: written as one expression it compiles to a branch)
+    const float near = fmaf(fmaf(-d, q, v), r, q), far = v * __builtin_amdgcn_fmed3f(v, 0.f, 1.f);
+    return fabsf(v) < 88.f ? near : far;
 }
 
 // Four floats as three bf16 quads (rounded, not cut: the terms alternate in sign, and the
