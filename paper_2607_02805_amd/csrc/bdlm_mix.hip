@@ -71,16 +71,20 @@ typedef __attribute__((address_space(1))) const float g_f;
 
 __device__ __forceinline__ float ex2(float v) { return __builtin_amdgcn_exp2f(v); }
 
-// v / (1 + e^-v): the quotient of the hardware reciprocal is corrected by its remainder (a
-// rounding of the quotient, as a division gives).  Past 88 either way, where e^-v or its
-// reciprocal leaves the range, it is v or 0 (infinities: +inf and NaN, as the division gives).
-__device__ __forceinline__ float silu(float v) {
-    const float d = 1.f + ex2(v * -kLog2e);
-    const float r = __builtin_amdgcn_rcpf(d);
+// v / (1 + e^-v) = q + t r: a quotient q by the hardware reciprocal r and its remainder t = (v - q)
+// - q e^-v, which does without the rounding of 1 + e^-v (v - q is exact for v >= 0, where the
+// function is large).  Past 88 either way q is v or 0 by itself (infinities: +inf and NaN, as a
+// division gives), and the remainder, in which infinities would meet, is left out.
+struct Silu {
+    float q, r, t;
+};
+__device__ __forceinline__ Silu silu(float v) {
+    const float e = ex2(v * -kLog2e);
+    const float r = __builtin_amdgcn_rcpf(1.f + e);
     const float q = v * r;
-    // (both formed, then one selected: written as one expression it compiles to a branch)
-    const float near = fmaf(fmaf(-d, q, v), r, q), far = v * __builtin_amdgcn_fmed3f(v, 0.f, 1.f);
-    return fabsf(v) < 88.f ? near : far;
+    // (formed, then selected: as one expression it compiles to a branch)
+    const float t = fmaf(-q, e, v - q);
+    return Silu{q, r, fabsf(v) < 88.f ? t : 0.f};
 }
 
 // Four floats as three bf16 quads (rounded, not cut: the terms alternate in sign, and the
@@ -104,9 +108,11 @@ __device__ __forceinline__ f32x4 mma_pair(uint4 a, uint4 b, f32x4 c) {
     return mma_k32(as_s16x4(uint2{a.x, a.y}), as_s16x4(uint2{a.z, a.w}), as_s16x4(uint2{b.x, b.y}),
                    as_s16x4(uint2{b.z, b.w}), c);
 }
-// c += a b over 32 contraction indices, both operands in three terms (smallest products first)
-__device__ __forceinline__ f32x4 mma6(const uint4 (&a)[3], const uint4 (&b)[3], f32x4 c) {
-    c = mma_pair(a[1], b[1], c);
+// a b over 32 contraction indices, both operands in three terms (smallest products first).  The
+// sum starts from zero and is added to an accumulator once: six products added to it one by one
+// would each round at its size.
+__device__ __forceinline__ f32x4 mma6(const uint4 (&a)[3], const uint4 (&b)[3]) {
+    f32x4 c = mma_pair(a[1], b[1], f32x4{0.f, 0.f, 0.f, 0.f});
     c = mma_pair(a[2], b[0], c);
     c = mma_pair(a[0], b[2], c);
     c = mma_pair(a[1], b[0], c);
@@ -167,7 +173,8 @@ struct ConvTask {
     }
     // channel e at the four tokens (past the block: some finite value, which meets source
     // weights of zero or rows that are not stored)
-    __device__ __forceinline__ f32x4 out(int e) const {
+    // (skip, unless null: the values times D, before the values' rounding)
+    __device__ __forceinline__ f32x4 out(int e, float D = 0.f, f32x4 *skip = nullptr) const {
         float v[7];
 #pragma unroll
         for (int i = 0; i < 7; ++i) {
@@ -186,7 +193,9 @@ struct ConvTask {
             float s = b[e];
 #pragma unroll
             for (int k = 0; k < 4; ++k) s += w[e][k] * (REV ? v[i + 3 - k] : v[i + k]);
-            o[i] = silu(s);
+            const Silu u = silu(s);
+            o[i] = fmaf(u.t, u.r, u.q);
+            if (skip) (*skip)[i] = fmaf(D, u.q, D * (u.t * u.r));
         }
         return o;
     }
@@ -494,7 +503,7 @@ bdlm_mix_kernel(const MixArgs a) {
 #pragma unroll
                 for (int z = 0; z < 3; ++z) sq[z] = sX[z * kP * SCH + s_at(16 * ct + col, 4 * k + grp)];
 #pragma unroll
-                for (int m = 0; m < MR; ++m) Y[m][ct] = mma6(cf[m], sq, Y[m][ct]);
+                for (int m = 0; m < MR; ++m) Y[m][ct] += mma6(cf[m], sq);
             }
         }
 #pragma unroll
@@ -547,8 +556,8 @@ bdlm_mix_kernel(const MixArgs a) {
             const f32x4 wt = *reinterpret_cast<const f32x4 *>((rev ? sWr : sWf) + t0);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const f32x4 o = tk.out(e);
-                sk[e] = (rev ? Dr : Df) * o;
+                const f32x4 o = rev ? tk.out(e) : tk.out(e, Df, &sk[e]);
+                if constexpr (rev) sk[e] = Dr * o;
                 const T3 s = split3(o * wt);
                 const int at = 2 * XI::at(4 * cq + e, wc) + whalf;
 #pragma unroll
@@ -598,7 +607,7 @@ bdlm_mix_kernel(const MixArgs a) {
 #pragma unroll
                         for (int z = 0; z < 3; ++z)
                             xq[z] = sX[z * XI::PLANE + XI::at(16 * ct + col, 4 * (jp - first) + grp)];
-                        T[ct] = mma6(M, xq, T[ct] * q);
+                        T[ct] = T[ct] * q + mma6(M, xq);
                     }
 #pragma unroll
                     for (int z = 0; z < 3; ++z) M[z] = N[z];
@@ -651,7 +660,7 @@ bdlm_mix_kernel(const MixArgs a) {
 #pragma unroll
                         for (int z = 0; z < 3; ++z)
                             xq[z] = sX[z * XI::PLANE + XI::at(16 * ct + col_, 4 * (own - first) + grp_)];
-                        Y[m][ct] = mma6(M, xq, Y[m][ct]);
+                        Y[m][ct] += mma6(M, xq);
                     }
                 }
             }
@@ -681,7 +690,7 @@ bdlm_mix_kernel(const MixArgs a) {
 #pragma unroll
                                 for (int z = 0; z < 3; ++z)
                                     xq[z] = sX[z * XI::PLANE + XI::at(16 * (c0 + c) + col, 4 * (jp - p0) + grp)];
-                                acc[k][c] = mma6(bc, xq, acc[k][c] * q);
+                                acc[k][c] = acc[k][c] * q + mma6(bc, xq);
                             }
 #pragma unroll
                             for (int z = 0; z < 3; ++z) bc[z] = bn[z];

@@ -67,3 +67,42 @@ def test_conv_long_blocks(H, N, L, bf16, G, fast, want_y):
     np.testing.assert_array_equal(got[[1, 3]], pool[[1, 3]].astype(np.float32))   # untouched slots
     np.testing.assert_array_equal(cp.cpu().numpy(), cache_ref.astype(np.float32))
     assert nc.tolist() == [L, 0, L, 0] and nb.tolist() == [1, 0, 1, 0]
+
+
+@pytest.mark.parametrize("N,L,bf16", [(128, 33, True), (128, 64, True), (128, 16, False), (16, 16, False),
+                                      (128, 100, False), (64, 256, True)])
+def test_error_of_fp32_products(N, L, bf16):
+    """Products of fp32 operands run as six products of bf16 terms; their sums must not round
+    more often than fp32 products would.  A rounding to fp32 of a value of its own size has a
+    relative rms of about 2.6e-8.  An output's operands (x, B and C after the convolution, the
+    state, the weights) and its own sums of at most eight 32-index products contribute a dozen
+    to two dozen of them, in quadrature below 1.25e-7 of the 2-norm.  A state's are about half a
+    dozen (6.5e-8), and per pair of tiles passed the decay's own error, which all of a head's
+    state shares: the hardware exponential's unit in the last place and the rounding of its
+    argument, 4e-8.  Six additions per 32 indices at the sum's size come to 1.5e-7 for outputs
+    at dstate 128 and to 1.1e-7 to 2.0e-7 for states of 16 to 100 tokens."""
+    import paper_2607_02805_amd as bd
+    H = 6
+    w = bi.Workload("t", 2, H, 64, N, 1, L, 0, bf16, 1, 12600 + N + L)
+    d = bi.block_inputs(w, 0)
+    # B and C of unit size, as before a convolution: the prefix term is most of the output
+    r = np.random.Generator(np.random.PCG64(12601))
+    for k in ("B", "C"):
+        v = r.standard_normal(d[k].shape).astype(np.float32)
+        d[k] = bi.to_bf16_bits(v) if bf16 else v
+    cw, cb = conv_params(w, 12602)
+    cache = r.standard_normal((2, 3, cw.shape[0])).astype(np.float32)
+    pool = bi.random_state(w, 2, 6, 0.5).astype(np.float64)
+    y_ref, fin = oracle_step(d, cw, cb, cache.astype(np.float64), pool, None)
+    *_, s_ref = oracle.block_step(fin, pool, parts=True, final_state=True)
+    v, h = to_dev(d), pool_dev(pool)
+    nc, nb = np.zeros(2, np.int64), np.zeros(2, np.int64)
+    y = bd.conv_commit_boundary(v["x"], v["dt"], v["A"], v["B"], v["C"], v["D"], v["D_rev"],
+                                torch.from_numpy(cw).to(DEV), torch.from_numpy(cb).to(DEV),
+                                torch.from_numpy(cache).to(DEV), h, nc, nb, y_clean=True)
+
+    def err(a, ref):
+        return float(np.linalg.norm(a.astype(np.float64) - ref) / np.linalg.norm(ref))
+    ey, es = err(y.cpu().numpy(), y_ref), err(from_pool(h), s_ref)
+    say("error of fp32 products", dict(N=N, L=L, bf16=bf16), "outputs", ey, "states", es)
+    assert ey <= 1.25e-7 and es <= (6.5e-8 ** 2 + (L + 31) // 32 * 4e-8 ** 2) ** 0.5
