@@ -816,10 +816,10 @@ bool mix_fits(const LaunchArgs &a) {
     // the Gram tiles and the split Cf and Bf live in the caller's convolution workspace, whose
     // size is that of the convolved inputs: too small only where there are few heads per group
     // or next to no tokens
-    // (rows are addressed with 31-bit byte offsets)
+    // (rows are addressed with 31-bit byte offsets, and a launch holds fewer than 2^32 threads)
     constexpr int64_t kMax = int64_t(1) << 31;
-    const int64_t es = a.bf16 ? 2 : 4;
-    return a.L >= 1 && a.L <= 256 && static_cast<int64_t>(a.batch) * a.ngroups < (int64_t(1) << 26) &&
+    const int64_t es = a.bf16 ? 2 : 4, nb = (a.L + 63) / 64;
+    return a.L >= 1 && a.L <= 256 && static_cast<int64_t>(a.batch) * a.ngroups * nb * (nb + 1) * 512 < 2 * kMax &&
            a.L * a.xs_t * es + 256 < kMax && a.L * a.bcs_t * es + 512 < kMax &&
            static_cast<int64_t>(a.L) * a.nheads * kP * 4 < kMax &&
            mix_plan(a).total <= conv_workspace(a.batch, a.L, a.nheads, a.ngroups, a.dstate);

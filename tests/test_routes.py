@@ -78,3 +78,24 @@ def test_masked_kernels_keep_the_strides_of_a_projection(rules, L):
     for H, G, N in ((1, 1, 16), (32, 1, 128), (26, 2, 64), (128, 8, 128)):
         row = 2 * H * 64 + 2 * G * N + H
         assert rules("masked", 16, H, G, L, N, 1, row, row, row)
+
+
+def test_convolution_blocks_launch_within_32_bits(rules):
+    """The Gram kernel's grid counts (row, group)s, up to 20 blocks of 512 threads each; a
+    launch holds fewer than 2^32 threads (the convolution and scan kernels take the rest)."""
+    r = random.Random(7)
+    took = 0
+    for _ in range(4000):
+        G = r.choice([1, 8, 64])
+        batch = 1 << r.randint(0, 22) if r.random() < 0.5 else r.randint(1, 1 << 22)
+        hpg = r.randint(1, 8)
+        L = r.choice([33, 64, 65, 128, 129, 192, 193, 256])
+        if batch * G * hpg > 1 << 22:
+            continue
+        if rules("mix", batch, G * hpg, G, L, r.choice([16, 128]), r.choice([0, 1])):
+            nb = (L + 63) // 64
+            took += 1
+            assert batch * G * nb * (nb + 1) * 512 < 1 << 32, (batch, G, hpg, L)
+    assert took > 500
+    assert not rules("mix", 6554, 192, 64, 193, 16, 1)       # 254 GB in all
+    assert rules("mix", 6553, 192, 64, 193, 16, 1)
