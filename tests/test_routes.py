@@ -97,5 +97,5 @@ def test_convolution_blocks_launch_within_32_bits(rules):
             took += 1
             assert batch * G * nb * (nb + 1) * 512 < 1 << 32, (batch, G, hpg, L)
     assert took > 500
-    assert not rules("mix", 6554, 192, 64, 193, 16, 1)       # 254 GB in all
-    assert rules("mix", 6553, 192, 64, 193, 16, 1)
+    assert rules("mix", 10922, 192, 64, 129, 16, 1)
+    assert not rules("mix", 10923, 192, 64, 129, 16, 1)      # 699,072 (row, group)s of 12 blocks
