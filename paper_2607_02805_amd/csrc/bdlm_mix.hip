@@ -222,16 +222,20 @@ __global__ void __launch_bounds__(512) bdlm_mix_gram_kernel(const MixArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, grp = lane >> 4;
     const int nb = (a.L + 63) / 64;
+    const bool want_y = a.y != nullptr;
     int u = blockIdx.x;
-    int ji = u % (nb + 1);
-    u /= nb + 1;
+    int ji = 0;
+    if (want_y) {
+        ji = u % (nb + 1);
+        u /= nb + 1;
+    }
     const int mi = u % nb;
     u /= nb;
     const int g = u % a.ngroups, b = u / a.ngroups;
+    if (!want_y) ji = mi;              // a commit without outputs: the diagonal's, for Bf^T
     const bool rev = ji > mi;
     if (rev) --ji;
-    const bool want_y = a.y != nullptr, diag = mi == ji && !rev;
-    if (!want_y && !(diag && a.commit)) return;
+    const bool diag = mi == ji && !rev;
     const int bg = b * a.ngroups + g;
     const int64_t slot = a.use_slots ? a.slots[b] : b;
     const int HP = a.nheads * kP, GN = a.ngroups * NS;
@@ -461,7 +465,8 @@ bdlm_mix_kernel(const MixArgs a) {
     // first request a share each of the lines, one word a line, into their L2.
     uint32_t warm = 0u;
     {
-        const int nl = nt * (np + 1) * 24, ncl = nt * (NP / 32) * 24, nbl = COMMIT ? QN * np * 24 : 0;   // 128-byte lines
+        // 128-byte lines (a commit without outputs reads Bf^T alone)
+        const int nl = want_y ? nt * (np + 1) * 24 : 0, ncl = want_y ? nt * (NP / 32) * 24 : 0, nbl = COMMIT ? QN * np * 24 : 0;
         for (int i = (h - g * a.heads_per_group) * NT + tid; i < nl + ncl + nbl; i += a.heads_per_group * NT) {
             const uint4 *src = i < nl ? gram - lane + i * 8 : (i < nl + ncl ? c3 - lane + (i - nl) * 8 : b3 - lane + (i - nl - ncl) * 8);
             warm ^= src->x;
@@ -790,7 +795,7 @@ hipError_t mix_head(const MixArgs &k, unsigned grid, hipStream_t s) {
 template <int NS, bool BF16>
 hipError_t mix_launch(const MixArgs &k, hipStream_t s) {
     const int nb = (k.L + 63) / 64;
-    const unsigned gg = static_cast<unsigned>(k.batch) * k.ngroups * nb * (nb + 1);
+    const unsigned gg = static_cast<unsigned>(k.batch) * k.ngroups * nb * (k.y ? nb + 1 : 1);
     hipLaunchKernelGGL((bdlm_mix_gram_kernel<NS, BF16>), dim3(gg), dim3(512), 0, s, k);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

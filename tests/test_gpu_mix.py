@@ -106,3 +106,30 @@ def test_error_of_fp32_products(N, L, bf16):
     ey, es = err(y.cpu().numpy(), y_ref), err(from_pool(h), s_ref)
     say("error of fp32 products", dict(N=N, L=L, bf16=bf16), "outputs", ey, "states", es)
     assert ey <= 1.25e-7 and es <= (6.5e-8 ** 2 + (L + 31) // 32 * 4e-8 ** 2) ** 0.5
+
+
+@pytest.mark.parametrize("H,N,L,bf16,G", [(4, 128, 256, True, 1), (6, 64, 200, False, 2), (3, 16, 65, True, 1),
+                                          (4, 32, 64, False, 1), (4, 128, 17, False, 1)])
+def test_commit_without_outputs_forms_the_same_states(H, N, L, bf16, G):
+    """Without outputs only the diagonal workgroups of the Gram kernel run, and the head kernel
+    reads the split B alone: the states and cached rows are those of a commit with outputs, bit
+    for bit, whatever the workspace held."""
+    import paper_2607_02805_amd as bd
+    w = bi.Workload("t", 3, H, 64, N, G, L, 0, bf16, 1, 12200 + N + L)
+    v = to_dev(bi.commit_inputs(w))
+    cw, cb = (torch.from_numpy(t).to(DEV) for t in conv_params(w, 12300 + L))
+    ws = torch.full((3 * L * (2 * H * 64 + 4 * G * N + H) * 4 + 256,), 0xff, dtype=torch.uint8, device=DEV)
+    got = []
+    for want_y in (False, True):
+        cp = torch.from_numpy(np.random.Generator(np.random.PCG64(6)).standard_normal((3, 3, cw.shape[0]))
+                              .astype(np.float32)).to(DEV)
+        h = pool_dev(bi.random_state(w, 3, 6, 0.5))
+        say("conv commit", dict(H=H, N=N, L=L, bf16=bf16, G=G, want_y=want_y))
+        bd.conv_commit_boundary(v["x"], v["dt"], v["A"], v["B"], v["C"], v["D"], v["D_rev"], cw, cb, cp, h,
+                                np.zeros(3, np.int64), np.zeros(3, np.int64), 0,
+                                y_clean=True if want_y else None, workspace=ws)
+        torch.cuda.synchronize()
+        got.append((h, cp))
+    assert torch.isfinite(got[0][0]).all()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
