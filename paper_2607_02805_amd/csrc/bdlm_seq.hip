@@ -1079,21 +1079,6 @@ hipError_t seq_out_both(const LaunchArgs &a, SeqArgs k, const SeqArgs &rev, unsi
     const hipError_t e = seq16_out(a.dstate, k, SeqOut::kBoth, grid, s);
     return e != hipSuccess ? e : seq16_out(a.dstate, rev, SeqOut::kPre, grid, s);
 }
-// Whether (row, head) pairs walk the whole sequence in one segment each, which spares the pass
-// for the states entering the segments (a third of the outputs' time) and the combination, but
-// leaves the chip to `units` workgroups.  A CU runs two of them (one at dstate 128 in fp32); a
-// last round of at most half the slots takes 0.6 of a full one.  Measured with outputs and
-// normalisation, one segment against several: 256 pairs of 8,192 tokens 666 us against 686,
-// 512 of 16,384 2,266 against 2,642, 640 of 4,096 785 against 857, 4,096 of 1,024 1,147
-// against 1,402.
-bool one_segment(const LaunchArgs &a) {
-    const int64_t units = static_cast<int64_t>(a.batch) * a.nheads;
-    const int64_t slots = !a.bf16 && a.dstate == 128 ? 256 : 512;
-    const int64_t rest = units % slots;
-    const double rounds = units / slots + (rest == 0 ? 0. : (2 * rest <= slots ? 0.6 : 1.));
-    return 2 * units >= slots && rounds * slots <= 1.33 * units;
-}
-
 SeqArgs seq_args(const LaunchArgs &a, int64_t T, const SeqPlan &pl, void *ws) {
     SeqArgs k;
     k.x = a.x;
@@ -1170,6 +1155,34 @@ hipError_t combine(const LaunchArgs &a, const SeqPlan &pl, const SeqArgs &k, flo
 
 }  // namespace
 
+// Whether (row, head) pairs walk the whole sequence in one segment each, which spares the pass
+// for the states entering the segments (a third of the outputs' time, half of it without
+// outputs) and the combination, but leaves the chip to `units` workgroups.  A CU runs two of
+// them, and a last round of at most half the slots takes 0.6 of a full one.  Measured with
+// outputs and normalisation, one segment against several: 256 pairs of 8,192 tokens 666 us
+// against 686, 512 of 16,384 2,266 against 2,642, 640 of 4,096 785 against 857, 4,096 of 1,024
+// 1,147 against 1,402.
+// In fp32 at dstate 128 a CU runs one (126 KB of LDS): a half-filled round takes a full one.
+// 4,096 tokens with outputs, one segment over several: 128 pairs 1.37, 256 0.75, 320 1.09, 352
+// 0.99, 448 0.84; block states alone: 128 1.01, 256 0.54, 320 0.84, 352 0.77.
+// block_len: tokens per block where the states entering blocks are written (0: a prefill).  Its
+// output pass walks a block per chunk, so blocks that fill little of a 64-token chunk leave less
+// to spare: one segment over several, with outputs, 832 pairs in blocks of 12 tokens 1.12 (dstate
+// 16), 256 in blocks of 20 1.09 (128).  At dstate 32 and less three smaller workgroups share a CU
+// and 256 pairs fill a third of the chip: in blocks of 48 1.08 to 1.21 (640 0.8 to 0.9, 256 in
+// blocks of 64 0.91 to 0.98), prefills of 7,300 tokens 1.18, of 1,024 1.0, of 300 0.7.
+bool one_segment(const LaunchArgs &a, int64_t T, int64_t block_len) {
+    const int64_t units = static_cast<int64_t>(a.batch) * a.nheads;
+    const bool alone = !a.bf16 && a.dstate == 128;
+    const int64_t slots = alone ? 256 : 512;
+    const bool part = a.y && block_len > 0 && block_len < 64 && block_len != 16 && block_len != 32;
+    if (a.y && a.dstate <= 32 && units <= 256 && (part || (block_len == 0 && T > 1024))) return false;
+    const double limit = part && block_len < 32 ? 1. + block_len / 128. : (alone && !a.y ? 1.67 : 1.33);
+    const int64_t rest = units % slots;
+    const double rounds = units / slots + (rest == 0 ? 0. : (2 * rest <= slots && !alone ? 0.6 : 1.));
+    return 2 * units >= slots && rounds * slots <= limit * units;
+}
+
 int launch_full_window(const LaunchArgs &a, int64_t T, void *ws, void *stream) {
     if (a.batch == 0 || T == 0) return BDLM_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1192,7 +1205,7 @@ int launch_prefill(const LaunchArgs &a, int64_t T, void *ws, void *stream, const
     if (a.batch == 0 || T == 0) return BDLM_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const SeqPlan pl = plan ? *plan : seq_plan(a.batch, a.nheads, a.dstate, T, 1);
-    if (pl.nseg == 1 || (a.y && one_segment(a))) {
+    if (pl.nseg == 1 || (a.y && one_segment(a, T, 0))) {
         // one segment per row and head: from the cached state and back to it in one launch
         SeqArgs k = one_segment_args(a, T);
         k.pool_in = a.h_pool;
@@ -1221,7 +1234,7 @@ int launch_boundary_states(const LaunchArgs &a, int64_t nblocks, const float *s_
     // the segments (seg_combine), then one sweep per segment, a block per chunk, that
     // writes every block's entering state (and the forward outputs if wanted)
     BoundaryPlan bp = boundary_plan(a.batch, a.nheads, a.dstate, nblocks, a.L);
-    if (one_segment(a)) {
+    if (one_segment(a, nblocks * a.L, a.L)) {
         bp.blocks_per_seg = nblocks;
         bp.nseg = 1;
         bp.state_bytes = 0;

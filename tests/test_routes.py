@@ -25,6 +25,13 @@ static LaunchArgs args(const int64_t *v) {
 extern "C" int masked(const int64_t *v) { return long_masked_fits(args(v)); }
 extern "C" int windows(const int64_t *v) { return masked_windows_fit(args(v)); }
 extern "C" int mix(const int64_t *v) { return mix_fits(args(v)); }
+// (L: tokens per block, 0 for a prefill; xs_t: tokens in all; the last value: outputs wanted)
+extern "C" int one_seg(const int64_t *v) {
+    LaunchArgs a = args(v);
+    float y;
+    a.y = v[9] ? &y : nullptr;
+    return one_segment(a, v[6], v[3]);
+}
 """
 
 
@@ -41,8 +48,8 @@ def rules(tmp_path_factory):
                     f"-Wl,-rpath,{os.path.dirname(bd.LIB_PATH)}"], check=True)
     lib = ctypes.CDLL(str(so))
 
-    def ask(rule, batch, H, G, L, N, bf16, xs_t=None, dts_t=None, bcs_t=None):
-        v = (ctypes.c_int64 * 9)(batch, H, G, L, N, bf16, xs_t or H * 64, dts_t or H, bcs_t or G * N)
+    def ask(rule, batch, H, G, L, N, bf16, xs_t=None, dts_t=None, bcs_t=None, last=0):
+        v = (ctypes.c_int64 * 10)(batch, H, G, L, N, bf16, xs_t or H * 64, dts_t or H, bcs_t or G * N, last)
         return bool(getattr(lib, rule)(v))
     return ask
 
@@ -99,3 +106,33 @@ def test_convolution_blocks_launch_within_32_bits(rules):
     assert took > 500
     assert rules("mix", 10922, 192, 64, 129, 16, 1)
     assert not rules("mix", 10923, 192, 64, 129, 16, 1)      # 699,072 (row, group)s of 12 blocks
+
+
+@pytest.mark.parametrize("units", [64, 96, 128, 160, 200, 224, 256, 300, 320, 384, 448, 512, 576, 640, 768, 1024, 2048])
+def test_one_segment_fills_the_chip(rules, units):
+    """fp32 at dstate 128 one workgroup fills a CU: pairs whose rounds leave more than a quarter
+    of the chip idle (two fifths without outputs) run in several segments."""
+    rounds = -(-units // 256) * 256
+    for L in (0, 32, 48, 64):
+        assert rules("one_seg", units, 1, 1, L, 128, 0, xs_t=4096, last=1) == (2 * units >= 256 and rounds <= 1.33 * units)
+        if L:
+            assert rules("one_seg", units, 1, 1, L, 128, 0) == (2 * units >= 256 and rounds <= 1.67 * units)
+    if units < 231:                                      # 0.45 of two workgroups per CU
+        assert not any(rules("one_seg", units, 1, 1, L, N, bf, last=y)
+                       for L in (0, 20, 48, 64) for N in (16, 64) for bf in (0, 1) for y in (0, 1))
+
+
+def test_one_segment_of_short_blocks(rules):
+    """Blocks that fill little of a chunk, with outputs (16 and 32 tokens share chunks), and
+    small states on a third of the chip."""
+    for N, bf in ((16, 1), (32, 0)):
+        assert not rules("one_seg", 256, 1, 1, 48, N, bf, last=1)
+        for L in (16, 32, 64):
+            assert rules("one_seg", 256, 1, 1, L, N, bf, last=1)
+        assert rules("one_seg", 256, 1, 1, 48, N, bf) and rules("one_seg", 640, 1, 1, 48, N, bf, last=1)
+        assert rules("one_seg", 256, 1, 1, 0, N, bf, xs_t=1024, last=1)
+        assert not rules("one_seg", 256, 1, 1, 0, N, bf, xs_t=1025, last=1)
+        assert rules("one_seg", 512, 1, 1, 0, N, bf, xs_t=1025, last=1)
+    assert rules("one_seg", 256, 1, 1, 48, 64, 1, last=1)
+    assert not rules("one_seg", 832, 1, 1, 12, 16, 1, last=1)
+    assert rules("one_seg", 832, 1, 1, 12, 16, 1) and rules("one_seg", 1024, 1, 1, 12, 16, 1, last=1)
