@@ -116,6 +116,9 @@ int launch_prefill(const LaunchArgs &a, int64_t T, void *ws, void *stream,
 // Whether a prefill with outputs (block_len 0), or the states entering blocks of block_len tokens
 // (outputs if a.y), of T tokens run as one segment per row and head.
 bool one_segment(const LaunchArgs &a, int64_t T, int64_t block_len);
+// Whether a prefill of T tokens without outputs, planned as one segment, runs in one launch.
+bool prefill_in_one(const LaunchArgs &a, int64_t T);
+
 // A prefill plan whose workspace fits in cap bytes: the standard plan if it fits, else
 // fewer and longer segments (the same computation with fewer workgroups).  False if
 // even one segment per row and head needs more than cap.

@@ -1183,6 +1183,25 @@ bool one_segment(const LaunchArgs &a, int64_t T, int64_t block_len) {
     return 2 * units >= slots && rounds * slots <= limit * units;
 }
 
+// Whether a prefill of T tokens without outputs whose plan has one segment runs as that one launch,
+// from the cached states and back to them, or as the states pass and the combination: the launch
+// spares two passes over the states, but the output pass's workgroups stage C too and fewer fit
+// on a CU, so its chunks take longer.  The limit is where both take as long.  One launch over two
+// at 2,048 row-heads and more: fp32 dstate 128, 128 tokens 0.8 to 1.04, 256 1.1 to 1.3, 1,024
+// 1.5 (to 512 row-heads 256 tokens 0.83 to 1.0, at 64 and fewer 1.02 to 1.06); 64, 256 tokens
+// 0.97, 512 1.15; 32, 320 tokens 0.96, 512 1.04; 16, all within 0.95 to 1.05 from 192; bf16
+// dstate 128, 640 tokens 0.99, 1,024 1.14; 64 and 32, 384 tokens 0.96, 1,024 1.2 and 1.1; 16,
+// 128 tokens 0.92, 256 1.06, 512 1.15 (to 1,536 row-heads 256 tokens 0.87 to 1.03).
+bool prefill_in_one(const LaunchArgs &a, int64_t T) {
+    const int64_t units = static_cast<int64_t>(a.batch) * a.nheads;
+    if (a.bf16) {
+        if (a.dstate == 16) return T <= (units > 1536 ? 128 : 256);
+        return T <= (a.dstate == 128 ? 640 : 384);
+    }
+    if (a.dstate == 128) return T <= (units > 512 || units <= 64 ? 128 : 256);
+    return T <= (a.dstate == 32 ? 320 : 256);
+}
+
 int launch_full_window(const LaunchArgs &a, int64_t T, void *ws, void *stream) {
     if (a.batch == 0 || T == 0) return BDLM_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1205,7 +1224,7 @@ int launch_prefill(const LaunchArgs &a, int64_t T, void *ws, void *stream, const
     if (a.batch == 0 || T == 0) return BDLM_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const SeqPlan pl = plan ? *plan : seq_plan(a.batch, a.nheads, a.dstate, T, 1);
-    if (pl.nseg == 1 || (a.y && one_segment(a, T, 0))) {
+    if (a.y ? pl.nseg == 1 || one_segment(a, T, 0) : pl.nseg == 1 && prefill_in_one(a, T)) {
         // one segment per row and head: from the cached state and back to it in one launch
         SeqArgs k = one_segment_args(a, T);
         k.pool_in = a.h_pool;

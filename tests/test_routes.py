@@ -32,6 +32,7 @@ extern "C" int one_seg(const int64_t *v) {
     a.y = v[9] ? &y : nullptr;
     return one_segment(a, v[6], v[3]);
 }
+extern "C" int in_one(const int64_t *v) { return prefill_in_one(args(v), v[3]); }
 """
 
 
@@ -136,3 +137,16 @@ def test_one_segment_of_short_blocks(rules):
     assert rules("one_seg", 256, 1, 1, 48, 64, 1, last=1)
     assert not rules("one_seg", 832, 1, 1, 12, 16, 1, last=1)
     assert rules("one_seg", 832, 1, 1, 12, 16, 1) and rules("one_seg", 1024, 1, 1, 12, 16, 1, last=1)
+
+
+# (dstate, bf16) -> [(row-heads, tokens up to which a prefill without outputs is one launch)]
+IN_ONE = {(128, 0): [(64, 128), (256, 256), (512, 256), (1024, 128), (4096, 128)], (64, 0): [(64, 256), (4096, 256)],
+          (32, 0): [(64, 320), (4096, 320)], (16, 0): [(64, 256), (4096, 256)], (128, 1): [(64, 640), (4096, 640)],
+          (64, 1): [(2048, 384)], (32, 1): [(2048, 384)], (16, 1): [(1024, 256), (2048, 128)]}
+
+
+@pytest.mark.parametrize("N,bf16", IN_ONE)
+def test_prefill_without_outputs(rules, N, bf16):
+    """Longer prompts run as the states pass and the combination, as they did before."""
+    for units, most in IN_ONE[N, bf16]:
+        assert rules("in_one", units, 1, 1, most, N, bf16) and not rules("in_one", units, 1, 1, most + 1, N, bf16)
