@@ -202,7 +202,8 @@ int launch_masked_windows(const LaunchArgs &a, bool commit, bool want_y, void *s
 // else launch_block_long.
 int launch_block_long_shared(const LaunchArgs &a, bool commit, bool want_y, void *stream);
 // A long block's step whose reverse branch has its own inputs (of fwd's shapes and strides):
-// the masked form, in one launch, where it fits, else launch_block_long.
+// the masked form, in one launch, where that is faster (sep_windows_fit), else launch_block_long.
+bool sep_windows_fit(const LaunchArgs &a);
 int launch_block_long_sep(const LaunchArgs &fwd, const LaunchArgs &rev, void *stream);
 
 // The convolution part of the boundary state, then the block step (commit: the

@@ -615,14 +615,29 @@ int launch_masked_windows(const LaunchArgs &a, bool commit, bool want_y, void *s
     return e == hipSuccess ? BDLM_OK : BDLM_E_LAUNCH;
 }
 
-// Separate reverse inputs: every size that fits, but for dstate 128 beyond 128 tokens on more
-// workgroups than CUs, where the four waves per SIMD leave too few registers to load ahead
-// (16 x 26, 256 tokens: 47.7 us, the two sequence passes 46.6).
+// Separate reverse inputs: every block of 65 to 128 tokens that fits (windows over the two
+// sequence passes 0.65 to 0.91).  Beyond, the block is padded to 256 tokens, where the passes walk
+// 64-token chunks and at dstate 64 and less three or more of their workgroups share a CU; windows
+// over passes, of 193 to 256 tokens | of 129 to 192 (32 heads):
+//   dstate 128  to 256 row-heads 0.8; beyond, four waves per SIMD leave too few registers to load
+//               ahead (16 x 26 x 256 tokens: 47.7 us, the passes 46.6)
+//   dstate 64   to 768 row-heads 0.82 to 0.99, to 1,536 0.97 to 1.07, from 2,048 0.90 to 1.04
+//               | to 256 0.97 to 1.03, beyond 1.0 to 1.29
+//   dstate 32   to 512 0.82 to 0.93, to 1,536 0.96 to 1.08, from 2,048 0.88 to 1.08
+//               | to 256 0.97 to 1.03, to 512 1.0 to 1.05, beyond 1.10 to 1.29
+//   dstate 16   to 512 0.89 to 1.03, beyond 1.03 to 1.20 | 1.07 to 1.47
+bool sep_windows_fit(const LaunchArgs &a) {
+    if (!long_masked_fits(a)) return false;
+    if (a.L <= 128) return true;
+    const int64_t units = static_cast<int64_t>(a.batch) * a.nheads;
+    if (a.dstate == 128) return units <= kCUs;
+    if (a.L <= 192) return a.dstate >= 32 && units <= kCUs;
+    return units <= (a.dstate == 64 ? 768 : 512) || (a.dstate >= 32 && units >= 2048);
+}
+
 int launch_block_long_sep(const LaunchArgs &fwd, const LaunchArgs &rev, void *stream) {
     if (fwd.batch == 0 || fwd.L == 0) return BDLM_OK;
-    const int64_t units = static_cast<int64_t>(fwd.batch) * fwd.nheads;
-    if (!long_masked_fits(fwd) || (fwd.dstate == 128 && fwd.L > 128 && units > kCUs))
-        return launch_block_long(fwd, rev, false, true, stream);
+    if (!sep_windows_fit(fwd)) return launch_block_long(fwd, rev, false, true, stream);
     const WindowArgs k = window_args(fwd, rev, true);
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;

@@ -32,6 +32,7 @@ extern "C" int one_seg(const int64_t *v) {
     a.y = v[9] ? &y : nullptr;
     return one_segment(a, v[6], v[3]);
 }
+extern "C" int sep(const int64_t *v) { return sep_windows_fit(args(v)); }
 extern "C" int in_one(const int64_t *v) { return prefill_in_one(args(v), v[3]); }
 """
 
@@ -150,3 +151,17 @@ def test_prefill_without_outputs(rules, N, bf16):
     """Longer prompts run as the states pass and the combination, as they did before."""
     for units, most in IN_ONE[N, bf16]:
         assert rules("in_one", units, 1, 1, most, N, bf16) and not rules("in_one", units, 1, 1, most + 1, N, bf16)
+
+
+@pytest.mark.parametrize("N", [16, 32, 64, 128])
+def test_separate_reverse_inputs(rules, N):
+    """Beyond 128 tokens the windows pay for 256: three quarters of them at least, and fewer
+    row-heads the smaller the state."""
+    for units in (1, 32, 256, 257, 512, 513, 768, 769, 1024, 2047, 2048, 4096):
+        took = {L: rules("sep", 1, units, 1, L, N, 1) for L in (65, 128, 129, 192, 193, 256, 257)}
+        assert took[65] and took[128] and not took[257]
+        assert took[129] == took[192] == (N >= 32 and units <= 256)
+        few = units <= {16: 512, 32: 512, 64: 768, 128: 256}[N]
+        assert took[193] == took[256] == (few or (32 <= N <= 64 and units >= 2048))
+        assert not rules("sep", 1, units, 1, 256, N, 0)                        # fp32
+        assert not rules("sep", 1, units, 1, 256, N, 1, xs_t=8 << 20)          # past 2 GiB
