@@ -116,6 +116,8 @@ int launch_prefill(const LaunchArgs &a, int64_t T, void *ws, void *stream,
 // Whether a prefill with outputs (block_len 0), or the states entering blocks of block_len tokens
 // (outputs if a.y), of T tokens run as one segment per row and head.
 bool one_segment(const LaunchArgs &a, int64_t T, int64_t block_len);
+// Whether both bf16 branches of T tokens from one input set run as a forward and a reverse pass.
+bool seq_two_passes(const LaunchArgs &a, int64_t T);
 // Whether a prefill of T tokens without outputs, planned as one segment, runs in one launch.
 bool prefill_in_one(const LaunchArgs &a, int64_t T);
 

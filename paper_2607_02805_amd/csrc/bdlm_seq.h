@@ -43,11 +43,12 @@ struct SeqArgs {
 
 // What one output launch of the bf16 kernels of bdlm_seq16.hip computes.
 enum class SeqOut {
-    kFwd,    // the forward branch; stores y (only where seq16_pairs)
+    kFwd,    // the forward branch; stores y (only where seq16_forward)
     kBoth,   // the forward branch and the reverse branch's part within each chunk; stores y
     kPre,    // the reverse branch's part from later chunks, added onto y (after kBoth)
 };
 bool seq16_pairs(const SeqArgs &k, unsigned grid);
+bool seq16_forward(int ns, const SeqArgs &k, unsigned grid);
 hipError_t seq16_state(int ns, const SeqArgs &k, bool both, unsigned grid, hipStream_t s);
 hipError_t seq16_out(int ns, const SeqArgs &k, SeqOut what, unsigned grid, hipStream_t s);
 

@@ -1065,15 +1065,21 @@ hipError_t seq_state(const LaunchArgs &a, const SeqArgs &k, bool both, unsigned 
 }
 hipError_t seq_out(const LaunchArgs &a, const SeqArgs &k, bool rev, unsigned grid, hipStream_t s) {
     if (!a.bf16) return run_out<true>(a.dstate, k, rev, grid, s);
-    if (!rev && !k.emit && k.y && seq16_pairs(k, grid)) return seq16_out(a.dstate, k, SeqOut::kFwd, grid, s);
+    if (!rev && !k.emit && k.y && seq16_forward(a.dstate, k, grid)) return seq16_out(a.dstate, k, SeqOut::kFwd, grid, s);
     return run_out<false>(a.dstate, k, rev, grid, s);
 }
 // Both branches of one input set, k and rev the states entering every segment in their
-// directions (skips D and D_rev).  bf16 forms each chunk's decay-weighted C.B^T once, for both.
+// directions (skips D and D_rev).  bf16 forms each chunk's decay-weighted C.B^T once, for both,
+// but for calls of dstate 32 and less whose activations are larger than the caches (786,432
+// row-head tokens: 0.3 GB of x and y): there the forward and the reverse pass are as near the
+// memory's rate and issue less beside it.  Once for both over twice, dstate 16 | 32: 512
+// row-heads of 1,024 tokens 0.98 | 0.97, 1,024 of 1,024 1.03 | 0.99, 512 of 4,096 1.05 | 1.01,
+// 512 of 8,192 1.04 | 1.04, 4,096 of 1,024 1.08 | 1.04 (dstate 64: 0.92 to 0.98, 128: 0.88 to 0.96).
 hipError_t seq_out_both(const LaunchArgs &a, SeqArgs k, const SeqArgs &rev, unsigned grid, hipStream_t s) {
-    if (!a.bf16) {
-        const hipError_t e = run_out<true>(a.dstate, k, false, grid, s);
-        return e != hipSuccess ? e : run_out<true>(a.dstate, rev, true, grid, s);
+    if (!a.bf16 || seq_two_passes(a, k.T)) {
+        const hipError_t e = a.bf16 ? run_out<false>(a.dstate, k, false, grid, s) : run_out<true>(a.dstate, k, false, grid, s);
+        if (e != hipSuccess) return e;
+        return a.bf16 ? run_out<false>(a.dstate, rev, true, grid, s) : run_out<true>(a.dstate, rev, true, grid, s);
     }
     k.skip2 = rev.skip;
     const hipError_t e = seq16_out(a.dstate, k, SeqOut::kBoth, grid, s);
@@ -1154,6 +1160,10 @@ hipError_t combine(const LaunchArgs &a, const SeqPlan &pl, const SeqArgs &k, flo
 }
 
 }  // namespace
+
+bool seq_two_passes(const LaunchArgs &a, int64_t T) {
+    return a.dstate <= 32 && static_cast<int64_t>(a.batch) * a.nheads * T >= 3 << 18;
+}
 
 // Whether (row, head) pairs walk the whole sequence in one segment each, which spares the pass
 // for the states entering the segments (a third of the outputs' time, half of it without

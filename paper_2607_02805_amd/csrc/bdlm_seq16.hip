@@ -627,7 +627,7 @@ hipError_t out16(const SeqArgs &k, SeqOut what, unsigned grid, hipStream_t s) {
             if (kept) hipLaunchKernelGGL((bdlm_seg_out16_kernel<NS, 2, kFwd, true>), g, b, 0, s, k);
             else hipLaunchKernelGGL((bdlm_seg_out16_kernel<NS, 2, kFwd, false>), g, b, 0, s, k);
         } else {
-            return hipErrorInvalidValue;       // (bdlm_seq.hip's kernel: seq16_pairs)
+            return hipErrorInvalidValue;       // (bdlm_seq.hip's kernel: seq16_forward)
         }
     } else if (kept) {
         hipLaunchKernelGGL((bdlm_seg_out16_kernel<NS, HPW, kBoth, true>), g, b, 0, s, k);
@@ -660,6 +660,14 @@ hipError_t state16(const SeqArgs &k, bool both, unsigned grid, hipStream_t s) {
 // and smaller workgroups are faster: forward outputs of 640 row-heads 785 us against 799, of
 // 896 280 against 268, of 4,096 1,147 against 1,093 (one segment, normalisation included).
 bool seq16_pairs(const SeqArgs &k, unsigned grid) { return k.heads_per_group % 2 == 0 && grid >= 768; }
+// Forward outputs in pairs of heads (else bdlm_seq.hip's kernel).  At dstate 32 and less three of
+// the other's workgroups share a CU: pairs are faster only where they run in one round of two
+// per CU and the others need a second.  Pairs over the others, one segment of 1,024 tokens,
+// dstate 16 | 32: 768 row-heads 1.25 | 1.18, 896 0.90 | 0.86, 1,024 0.87 | 0.87, 1,280 1.09 |
+// 1.11; several segments of 4,096 tokens, 288 row-heads 1.09 | 1.08 (dstate 64: 0.99, 128: 0.98).
+bool seq16_forward(int ns, const SeqArgs &k, unsigned grid) {
+    return seq16_pairs(k, grid) && (ns >= 64 || (k.nseg == 1 && grid > 768 && grid <= 1024));
+}
 
 hipError_t seq16_state(int ns, const SeqArgs &k, bool both, unsigned grid, hipStream_t s) {
     switch (ns) {

@@ -15,6 +15,7 @@ import paper_2607_02805_amd as bd
 
 SHIM = r"""
 #include "bdlm_launch.h"
+#include "bdlm_seq.h"
 using namespace bdlm;
 static LaunchArgs args(const int64_t *v) {
     LaunchArgs a = {};
@@ -33,6 +34,13 @@ extern "C" int one_seg(const int64_t *v) {
     return one_segment(a, v[6], v[3]);
 }
 extern "C" int sep(const int64_t *v) { return sep_windows_fit(args(v)); }
+extern "C" int two(const int64_t *v) { return seq_two_passes(args(v), v[3]); }
+extern "C" int pairs(const int64_t *v) {   // v[3]: segments
+    SeqArgs k = {};
+    k.heads_per_group = v[1] / v[2];
+    k.nseg = v[3];
+    return seq16_forward(v[4], k, v[0] * v[1] * v[3]);
+}
 extern "C" int in_one(const int64_t *v) { return prefill_in_one(args(v), v[3]); }
 """
 
@@ -44,7 +52,8 @@ def rules(tmp_path_factory):
     src, so = d / "shim.cpp", d / "shim.so"
     src.write_text(SHIM)
     csrc = os.path.join(os.path.dirname(bd.LIB_PATH), "csrc")
-    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", f"-I{csrc}",
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                    "-isystem", "/opt/rocm/include", f"-I{csrc}",
                     f"-I{os.path.dirname(bd.HEADER_PATH)}", str(src), "-o", str(so),
                     f"-L{os.path.dirname(bd.LIB_PATH)}", "-l:libbdlm.so",
                     f"-Wl,-rpath,{os.path.dirname(bd.LIB_PATH)}"], check=True)
@@ -165,3 +174,22 @@ def test_separate_reverse_inputs(rules, N):
         assert took[193] == took[256] == (few or (32 <= N <= 64 and units >= 2048))
         assert not rules("sep", 1, units, 1, 256, N, 0)                        # fp32
         assert not rules("sep", 1, units, 1, 256, N, 1, xs_t=8 << 20)          # past 2 GiB
+
+
+@pytest.mark.parametrize("N", [16, 32, 64, 128])
+def test_both_branches_of_large_calls(rules, N):
+    """Small states and activations beyond the caches: a forward and a reverse pass."""
+    for units in (1, 96, 512, 4096):
+        T = -(-(3 << 18) // units)
+        assert rules("two", units, 1, 1, T, N, 1) == (N <= 32)
+        assert not rules("two", units, 1, 1, T - 1, N, 1)
+
+
+@pytest.mark.parametrize("N", [16, 32, 64, 128])
+def test_forward_outputs_in_pairs_of_heads(rules, N):
+    """Small states: only where pairs take one round and single heads two."""
+    for rows, segs in ((23, 1), (24, 1), (25, 1), (32, 1), (33, 1), (64, 1), (28, 1), (14, 2), (7, 8)):
+        grid = 32 * rows * segs
+        took = rules("pairs", rows, 32, 1, segs, N, 1)
+        assert took == (grid >= 768 and (N >= 64 or (segs == 1 and 768 < grid <= 1024)))
+        assert not rules("pairs", rows, 32, 32, segs, N, 1)      # one head per group
