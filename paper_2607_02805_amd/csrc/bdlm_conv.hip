@@ -215,6 +215,27 @@ __global__ void __launch_bounds__(256) bdlm_conv_keep_kernel(const ConvArgs a) {
 
 }  // namespace
 
+// The Gram and head kernels work on 64 tokens at least, so on many row-heads of a few tokens, and
+// at dstate 128 where their loads are longest, the convolution kernel and the block kernel's fp32
+// products are faster.  Measured in fp32, Gram and head kernels over those:
+//   33 tokens and more 0.25 to 0.8 (without outputs, where the other is a forward pass alone, 129 to
+//     192 tokens 0.95 to 1.16, 256 tokens 0.86 to 1.09)
+//   steps, dstate 128: to 8 tokens 1.1 to 1.35; 16 tokens to 1,024 row-heads 1.02 to 1.27, from
+//     2,048 1.0; 17 to 32 tokens to 128 row-heads 0.97 to 1.17, beyond 0.55 to 1.03
+//   steps, dstate 64 and less: to 8 tokens from 1,024 row-heads 1.07 to 2.1, on fewer 0.9 to 1.14;
+//     dstate 16, 12 tokens from 2,048 row-heads 1.09 to 1.24
+//   commits: to 4 tokens from 1,024 row-heads 1.0 to 1.6; 8 tokens 0.8 to 1.22, 16 tokens 0.76 to 1.18
+// Where they are a few percent slower, and in commits to a fifth, they are kept, since they are the
+// more exact: 16 tokens, states 4.0e-8 from 64 bits against 1.16e-7, outputs at dstate 16 to 64
+// 7.7e-8 to 9.1e-8 against 8.5e-8 to 1.2e-7.
+bool mix_pays(const LaunchArgs &a, bool commit) {
+    const int64_t units = static_cast<int64_t>(a.batch) * a.nheads;
+    if (a.L > 32) return true;
+    if (commit) return a.L > 4 || units < 1024;
+    if (a.dstate == 128) return a.L > 16 ? units > 128 : a.L > 8 && units >= 2048;
+    return a.L > (a.dstate == 16 && units >= 2048 ? 12 : 8) || units < 1024;
+}
+
 int launch_conv_block(const LaunchArgs &a, const float *w, const float *bias, float *conv_pool,
                       bool commit, void *ws, void *stream) {
     if (a.batch == 0 || a.L == 0) return BDLM_OK;
@@ -255,11 +276,11 @@ int launch_conv_block(const LaunchArgs &a, const float *w, const float *bias, fl
                            static_cast<hipStream_t>(stream), k);
         return hipGetLastError() == hipSuccess ? BDLM_OK : BDLM_E_LAUNCH;
     }
-    // other blocks of up to 256 tokens: the Gram kernel and the head kernel of bdlm_mix.hip (with
-    // 33 tokens and more 2.0 to 2.8 times faster than what follows here; up to 32 bf16 tokens
-    // the one launch above is faster: 47 against 52 us for step, normalisation and commit at
-    // 32 heads, dstate 128, 32 tokens, batch 16, and 18 against 25 us at 4 heads, batch 1)
-    if (mix_fits(a)) return launch_mix(a, w, bias, conv_pool, commit, ws, stream);
+    // other blocks of up to 256 tokens: the Gram kernel and the head kernel of bdlm_mix.hip, where
+    // they are faster than what follows here (mix_pays; up to 32 bf16 tokens the one launch
+    // above is faster: 47 against 52 us for step, normalisation and commit at 32 heads, dstate
+    // 128, 32 tokens, batch 16, and 18 against 25 us at 4 heads, batch 1)
+    if (mix_fits(a) && mix_pays(a, commit)) return launch_mix(a, w, bias, conv_pool, commit, ws, stream);
     const dim3 cgrid((ch + kCT * kCV - 1) / (kCT * kCV), a.batch, (a.L + kTT - 1) / kTT);
     if (a.bf16)
         hipLaunchKernelGGL(bdlm_conv_kernel<true>, cgrid, dim3(kCT), 0, static_cast<hipStream_t>(stream), k);

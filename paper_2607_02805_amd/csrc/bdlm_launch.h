@@ -57,6 +57,8 @@ int launch_conv_fused(const LaunchArgs &a, const float *w, const float *bias, co
 // kernel per (row, group), then one workgroup per (row, head) computing both branches; a
 // commit also replaces the cached input rows.  a.y may be nullptr for a commit.
 bool mix_fits(const LaunchArgs &a);
+// Whether they are faster there than the convolution kernel and the scan kernels (bdlm_conv.hip).
+bool mix_pays(const LaunchArgs &a, bool commit);
 int launch_mix(const LaunchArgs &a, const float *w, const float *bias, float *conv_pool, bool commit,
                void *ws, void *stream);
 

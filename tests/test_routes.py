@@ -41,6 +41,7 @@ extern "C" int pairs(const int64_t *v) {   // v[3]: segments
     k.nseg = v[3];
     return seq16_forward(v[4], k, v[0] * v[1] * v[3]);
 }
+extern "C" int pays(const int64_t *v) { return mix_pays(args(v), v[9]); }   // (v[9]: a commit)
 extern "C" int in_one(const int64_t *v) { return prefill_in_one(args(v), v[3]); }
 """
 
@@ -193,3 +194,20 @@ def test_forward_outputs_in_pairs_of_heads(rules, N):
         took = rules("pairs", rows, 32, 1, segs, N, 1)
         assert took == (grid >= 768 and (N >= 64 or (segs == 1 and 768 < grid <= 1024)))
         assert not rules("pairs", rows, 32, 32, segs, N, 1)      # one head per group
+
+
+@pytest.mark.parametrize("N", [16, 32, 64, 128])
+def test_short_convolution_blocks(rules, N):
+    """The Gram and head kernels work on 64 tokens: many row-heads of a few fp32 tokens, and at
+    dstate 128 steps of any number, stay with the convolution and block kernels."""
+    for units in (1, 16, 128, 129, 1023, 1024, 2047, 2048, 4096):
+        def pays(commit, L):
+            return rules("pays", units, 1, 1, L, N, 0, last=commit)
+        for L in (33, 64, 65, 256):
+            assert pays(0, L) and pays(1, L)
+        for L in (1, 4, 5, 8, 9, 12, 13, 16, 17, 32):
+            assert pays(1, L) == (L > 4 or units < 1024)
+            if N == 128:
+                assert pays(0, L) == (units > 128 if L > 16 else L > 8 and units >= 2048)
+            else:
+                assert pays(0, L) == (units < 1024 or L > (12 if N == 16 and units >= 2048 else 8))
