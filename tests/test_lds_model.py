@@ -152,7 +152,7 @@ def new_model(arrays):
 
 
 # ------------------------------------------------------------- sequence kernels
-def stage_chunk(m, NS, with_c, instr0=0, with_wr=False):
+def stage_chunk(m, NS, with_c, instr0=0):
     """Stager::stage (bf16 storage): row images of B (and C when loaded) and of x from
     the registers of one chunk; plus wave 0's decay sums."""
     BCPR = NS // 8
@@ -182,7 +182,7 @@ def stage_chunk(m, NS, with_c, instr0=0, with_wr=False):
                 for pq in (2 * pc, 2 * pc + 1):
                     m.access(tid, "W", instr0 + 3, "sX", x_slot(t, pq) * 8, 8, tag=("sX", t, 4 * pq))
     for lane in range(64):                    # wave 0: decay sums
-        for arr in ("sDt", "sCs", "sEc", "sWs") + (("sWr",) if with_wr else ()):
+        for arr in ("sDt", "sCs", "sEc", "sWs"):
             if arr in m.arrays:
                 m.access(lane, "W", instr0 + 4, arr, lane * 4, 4, tag=(arr, lane))
 
@@ -205,30 +205,6 @@ def read_xt(m, tid, instr):
     for jt in range(4):
         t, pq = 16 * jt + tr_tok(lane), 4 * wave + tr_quad(lane)
         m.access(tid, "R", instr, "sX", x_slot(t, pq) * 8, 8, tag=("sX", t, 4 * pq))
-
-
-def seg_state_model(NS, both):
-    QN = NS // 16
-    arrays = {"sB": 4 * QN * 64 * 8, "sX": 16 * P * 8}
-    for a in ("sDt", "sCs", "sEc", "sWs", "sWr"):
-        arrays[a] = KC * 4
-    m = new_model(arrays)
-    m.barrier()                                # kernel start / previous chunk's last barrier
-    stage_chunk(m, NS, with_c=False, with_wr=both)
-    m.barrier()
-    for tid in range(THREADS):
-        grp = (tid & 63) >> 4
-        m.access(tid, "R", 10, "sCs", (KC - 1) * 4, 4, tag=("sCs", KC - 1))
-        read_xt(m, tid, 11)
-        for jt in range(4):
-            for r in range(4):
-                t = 16 * jt + 4 * grp + r
-                m.access(tid, "R", 12, "sWs", t * 4, 4, tag=("sWs", t))
-                if both:
-                    m.access(tid, "R", 12, "sWr", t * 4, 4, tag=("sWr", t))
-        read_bt(m, tid, NS, 13)
-    m.barrier()                                # end of chunk
-    return m
 
 
 def seg_out_model(NS, sub, want_y=True, carry=True):
@@ -603,12 +579,6 @@ def mask_model(NS, MT, commit, want_y=True):
                     rd(63, "sB", e * 8, 8, tag=("sB", 16 * jt + tt, 16 * q + 4 * ta))
     m.barrier()
     return m
-
-@pytest.mark.parametrize("NS", [16, 32, 64, 128])
-@pytest.mark.parametrize("both", [False, True])
-def test_seg_state_lds(NS, both):
-    assert seg_state_model(NS, both).check() == []
-
 
 @pytest.mark.parametrize("NS", [16, 32, 64, 128])
 @pytest.mark.parametrize("sub", [0, 16, 32])
