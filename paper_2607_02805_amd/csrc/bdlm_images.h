@@ -10,7 +10,10 @@
 
 namespace bdlm {
 
-// Row images, permuted so that every access pattern meets distinct banks.  B, C: 16-byte piece
+// Row images, permuted so that staging and operand reads meet each of 64 banks once, by the lanes
+// that move 256 bytes.  (The counters still show conflicts in 17 to 28 % of the sequence
+// kernels' LDS cycles, a part of them from weighted tiles written 8 bytes in every 16, which
+// are not in these images.)  B, C: 16-byte piece
 // c of token t (staging writes whole rows, operand reads 16 tokens by one piece).
 template <int NS>
 __device__ __forceinline__ int c_at(int t, int c) {

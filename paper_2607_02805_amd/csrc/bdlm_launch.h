@@ -43,12 +43,11 @@ int launch_block_pair(const LaunchArgs &fwd, const LaunchArgs &rev, bool commit,
                       void *stream);
 
 // A step (or commit) of a block of at most 32 tokens with the convolution part of the
-// boundary state, bf16 inputs before the convolution: the convolution runs while each
-// launch stages its inputs (forward launch from the cached rows conv_pool, then the
-// reverse launch zero-padded past the block), with no workspace.  The forward launch
-// stores y (none when want_y is false) and a commit updates the state; the reverse
-// launch adds onto y.  conv_pool is only read: a commit's new cache rows are written
-// by the caller afterwards.
+// boundary state, bf16 inputs before the convolution, in one launch with no workspace:
+// while it stages its inputs it convolves them both ways, forward from the cached rows
+// conv_pool and reverse zero-padded past the block.  It stores y (none when want_y is
+// false) and a commit updates the state.  conv_pool is only read: a commit's new cache
+// rows are written by the caller afterwards.
 int launch_conv_fused(const LaunchArgs &a, const float *w, const float *bias, const float *conv_pool,
                       bool commit, bool want_y, void *stream);
 
@@ -213,7 +212,8 @@ int launch_block_long_sep(const LaunchArgs &fwd, const LaunchArgs &rev, void *st
 // The convolution part of the boundary state, then the block step (commit: the
 // commit) on the convolved inputs: a.x / a.Bm / a.Cm are the pre-convolution inputs,
 // conv_pool [nslots][3][channels] the cached input rows (a commit replaces them).
-// ws: conv_workspace bytes (fp32 convolved x, B, C for both branches and dt).
+// ws: conv_workspace bytes: what the route of the call keeps there, nothing (launch_conv_fused),
+// Gram tiles and split operands (launch_mix), or fp32 convolved x, B, C for both branches and dt.
 int launch_conv_block(const LaunchArgs &a, const float *w, const float *bias, float *conv_pool,
                       bool commit, void *ws, void *stream);
 inline int64_t conv_workspace(int64_t batch, int64_t L, int64_t nheads, int64_t ngroups,

@@ -171,13 +171,14 @@ __device__ __forceinline__ int tr_quad(int lane) { return lane & 3; }
 // One chunk's global loads into registers and their staging into LDS.  Local token
 // i of chunk c is the segment's token 64c + i (reverse: its 64c + i-th token from
 // the end); row(i) is its position in the chunk's memory window.  bf16 storage stages
-// row images only (B, C when loaded, x), read transposed where the contraction runs
-// over tokens; fp32 storage stages row images of B and C and transposed images of B
-// and x (quads of four tokens' fp32 values).
+// row images (B, C, x), read transposed where the contraction runs over tokens; fp32
+// storage stages transposed images of B and x (quads of four tokens' fp32 values) and, when
+// C is loaded, row images of B and C.
 template <int NS, bool F32, bool REV, bool LOADC>
 struct Stager {
     using G = Geo<NS, F32>;
     static constexpr int ES = F32 ? 4 : 2;
+    static_assert(F32 || LOADC, "bf16 segment states run on bdlm_seg_state16_kernel");
 
     const char *xg, *dtg, *Bg, *Cg;  // this (row, head / group) at token 0
     int64_t xrow, dtrow, bcrow;      // bytes between consecutive tokens
@@ -295,7 +296,7 @@ struct Stager {
     }
 
     // Write the registers of the current chunk into LDS.  sb, sc: row images of B and
-    // C (B always for bf16 storage, both only when C is loaded for fp32); bt: the
+    // C (fp32: only when C is loaded); bt: the
     // transposed B image (fp32 only); xt: x, a row image (bf16) or transposed (fp32).
     __device__ __forceinline__ void stage(int tid, uint2 *sb, uint2 *sc, uint2 *bt,
                                           typename XQuad<F32>::T *xt) const {
@@ -304,8 +305,10 @@ struct Stager {
             const int task = tid + kThreads * k;
             if (task < G::BT) {
                 const int g = task / G::BCPR, pc = task % G::BCPR;
-                if constexpr (LOADC || !F32) row_image(rb[k], g, pc, sb);
-                if constexpr (LOADC) row_image(rc[k], g, pc, sc);
+                if constexpr (LOADC) {
+                    row_image(rb[k], g, pc, sb);
+                    row_image(rc[k], g, pc, sc);
+                }
                 if constexpr (F32) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -438,15 +441,12 @@ __device__ __forceinline__ void setup(ST &st, const SeqArgs &a, const Unit &un, 
 // ------------------------------------------------------------------ seg_state
 // Local forward state F (and, BOTH, reverse state R) of one segment from zero, and
 // the segment's total log2-decay.
-// (fp32 storage; bf16 runs on bdlm_seg_state16_kernel)
+// (fp32 storage: B and x as transposed fp32 images; bf16 runs on bdlm_seg_state16_kernel)
 template <int NS, bool BOTH>
 __global__ void __launch_bounds__(kThreads, 1) bdlm_seg_state_kernel(const SeqArgs a) {
-    constexpr bool F32 = true;
-    using G = Geo<NS, F32>;
-    constexpr int QN = G::QN;
-    // B: bf16 row image (read transposed) or fp32 transposed image; x likewise
-    __shared__ __align__(16) uint2 sBt[F32 ? 2 * 16 * NS : G::IMG];
-    __shared__ __align__(16) typename XQuad<F32>::T sXt[16 * kP];
+    constexpr int QN = NS / 16;
+    __shared__ __align__(16) uint2 sBt[2 * 16 * NS];
+    __shared__ __align__(16) f32x4 sXt[16 * kP];
     __shared__ __align__(16) float sDt[kC], sCs[kC], sEc[kC], sWs[kC], sWr[kC];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -456,7 +456,7 @@ __global__ void __launch_bounds__(kThreads, 1) bdlm_seg_state_kernel(const SeqAr
     const Unit un = decode(a);
     const int g = un.h / a.heads_per_group;
 
-    Stager<NS, F32, false, false> st;
+    Stager<NS, true, false, false> st;
     setup(st, a, un, g, tid, lane);
     const int nch = st.nchunks();
     const float A2 = a.A[un.h] * kLog2e;
@@ -468,35 +468,33 @@ __global__ void __launch_bounds__(kThreads, 1) bdlm_seg_state_kernel(const SeqAr
         if constexpr (BOTH) R[q] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     float off = 0.f;   // log2-decay of the segment's tokens before the current chunk
-    // forward-only segment states become cached or emitted states: three-term splits
-    constexpr bool T3 = !BOTH;
 
     st.issue(0, tid, wave, lane);
     for (int c = 0; c < nch; ++c) {
-        st.stage(tid, sBt, nullptr, sBt, sXt);
+        st.stage(tid, nullptr, nullptr, sBt, sXt);
         if (wave == 0)
             decay_sums<BOTH>(st.dt_value(c), A2, lane, sDt, sCs, sEc, sWs, sWr);
         __syncthreads();
         if (c + 1 < nch) st.issue(c + 1, tid, wave, lane);
 
         const float tot = sCs[kC - 1];
-        WOps<F32, T3> wf, wr;
+        WOps<true> wf, wr;
 #pragma unroll
         for (int jt = 0; jt < 4; ++jt) {
             s16x4 xh;
             f32x4 xv;
-            x_operand<F32>(sXt, jt, wave, lane, xh, xv);
+            x_operand<true>(sXt, jt, wave, lane, xh, xv);
             w_set(wf, jt, *reinterpret_cast<const f32x4 *>(&sWs[16 * jt + 4 * grp]) * xv);
             if constexpr (BOTH)
                 w_set(wr, jt,
                            *reinterpret_cast<const f32x4 *>(&sWr[16 * jt + 4 * grp]) * xv * ex2(off));
         }
         const float keep = ex2(tot);
-        BtOps<F32> cur, nxt;
-        bt_read<NS, F32>(cur, sBt, 0, lane);
+        BtOps<true> cur, nxt;
+        bt_read<NS, true>(cur, sBt, 0, lane);
 #pragma unroll
         for (int q = 0; q < QN; ++q) {
-            if (q + 1 < QN) bt_read<NS, F32>(nxt, sBt, q + 1, lane);
+            if (q + 1 < QN) bt_read<NS, true>(nxt, sBt, q + 1, lane);
             F[q] = bt_mma(cur, wf, F[q] * keep);
             if constexpr (BOTH) R[q] = bt_mma(cur, wr, R[q]);
             if (q + 1 < QN) cur = nxt;
