@@ -133,14 +133,44 @@ def test_tensors_off_the_gpu_are_refused_as_before(monkeypatch, name):
     assert native.taken == 0 and err is not None and err == err2
 
 
+@pytest.mark.gpu
 def test_intercepted_calls_are_left_to_python():
-    """Tensor subclasses and modes see the operations that the Python code makes."""
+    """Tensor subclasses and modes see the operations that the Python code makes: calls that
+    the native module takes are left to Python under a mode, or with a subclass among them."""
+    from torch.overrides import TorchFunctionMode
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Functions(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    class Dispatch(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    class Sub(torch.Tensor):
+        pass
+
     n = bd._native()
-    v = _inputs(torch.float32, "cpu")
-    with torch.device("meta"):
-        assert n.gated_rmsnorm(v["x"], v["z"], v["nw"], 1e-5, 1, None, None) is NotImplemented
-    assert n.gated_rmsnorm(v["x"]) is NotImplemented
-    assert n.scan_block_step(*[None] * 11) is NotImplemented
+    v = _inputs(torch.float32, "cuda")
+    act = [v["x"], v["dt"], v["A"], v["B"], v["C"], v["D"], v["Dr"], v["h0"], None,
+           np.array([3, 1], np.int32), None]
+    y = torch.ones(B, L, H, 64, device="cuda")
+    norm = [y, v["z"], v["nw"], 1e-5, 1, None, None]
+    for f, args, tensors in ((n.scan_block_step, act, (0, 1, 2, 3, 4, 5, 6, 7)), (n.gated_rmsnorm, norm, (0, 1, 2))):
+        assert torch.is_tensor(f(*args))
+        for mode in (Functions, Dispatch):
+            with mode():
+                assert f(*args) is NotImplemented
+        with torch.device("meta"):
+            assert f(*args) is NotImplemented
+        for i in tensors:
+            sub = list(args)
+            sub[i] = args[i].as_subclass(Sub)
+            assert f(*sub) is NotImplemented
+        assert torch.is_tensor(f(*args))
+        assert f(*args[:-1]) is NotImplemented
+    torch.cuda.synchronize()
 
 
 def test_native_module_missing_is_loud(monkeypatch, tmp_path):
