@@ -21,9 +21,10 @@
 // A commit's state update runs over the windows before the outputs do (which then take them in
 // the opposite order): its accumulators and theirs would not fit side by side.
 //
-// What binds it: issue.  The vector ALU and matrix instructions of a SIMD's four waves hardly
-// overlap: at 416 workgroups of 256 tokens, dstate 128, they take 50,800 cycles of the 48,400
-// that the waves stay.  Measured as graph replays, before -> here (before: kSep as a forward and
+// What binds it: neither unit by itself.  Four waves per SIMD, kStep at 32 x 32, 96 tokens, dstate
+// 128 | kSep at 64 x 24, 128 tokens, dstate 64: the vector ALU is busy in 34 | 40 % of the cycles, the
+// matrix unit in 17 | 12 %; a wave waits for memory, LDS or a barrier 40 | 49 % of its time, and for
+// an issue slot, all four being at the same stage, 41 | 24 %.  Measured as graph replays, before -> here (before: kSep as a forward and
 // a reverse sequence pass; one set in bdlm_mask.hip, one workgroup per CU):
 //   kSep   1 row x 26 heads, 256 tokens, dstate 128   32.4 -> 25.3 us
 //          8 x 32, 256 tokens, dstate 128             38.3 -> 30.0 us

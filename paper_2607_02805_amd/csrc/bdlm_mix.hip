@@ -27,13 +27,15 @@
 //   and MFMAs.  A pair of tiles over which the state decays below 2^-60 takes a path of its
 //   own (pair_slow); the source weights stay at or above 2^-60, so no factor overflows.
 //
-// Measured (26 heads, dstate 128, block 256, batch 16, bf16 inputs, traced): a step 18 + 56 us,
-// a commit 18 + 80 us, against 28 us for the convolution into an fp32 workspace and 85 + 82 us
+// Measured (26 heads, dstate 128, block 256, batch 16, bf16 inputs, traced): a step 19 + 60 us,
+// a commit 19 + 83 us, against 28 us for the convolution into an fp32 workspace and 85 + 82 us
 // for the sequence kernels' forward and reverse launches on it (fp32 MFMA), which blocks of
 // more than 256 tokens still take.  At 32 heads and 64 tokens, step and commit with the
-// normalisation between them: 64 us against 144.  What bounds the head kernel: vector ALU
-// (58 % of a SIMD's cycles, half of it the convolution and its split) and the matrix unit
-// (43 %), which overlap little because the two workgroups of a CU run in step.
+// normalisation between them: 68 us against 144.  What bounds the head kernel, step | commit: waves
+// wait for memory, LDS and barriers 51 | 60 % of their time and for an issue slot 28 | 23 %, with
+// the vector ALU busy in 33 | 28 % of the cycles (half of it the convolution and its split) and the
+// matrix unit in 22 | 21 %; the commit holds outputs and states side by side in 128 registers and
+// spills 39 (75 in fp32; 160 and 176 bytes a lane), the step 56 to 68 bytes a lane.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
