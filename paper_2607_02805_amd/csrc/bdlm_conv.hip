@@ -227,10 +227,11 @@ __global__ void __launch_bounds__(256) bdlm_conv_keep_kernel(const ConvArgs a) {
 //   commits: to 4 tokens from 1,024 row-heads 1.0 to 1.6; 8 tokens 0.8 to 1.22, 16 tokens 0.76 to 1.18
 // Where they are a few percent slower, and in commits to a fifth, they are kept, since they are the
 // more exact: 16 tokens, states 4.0e-8 from 64 bits against 1.16e-7, outputs at dstate 16 to 64
-// 7.7e-8 to 9.1e-8 against 8.5e-8 to 1.2e-7.
+// 7.7e-8 to 9.1e-8 against 8.5e-8 to 1.2e-7; and beyond 65,535 rows, which are the convolution
+// kernel's second grid dimension.
 bool mix_pays(const LaunchArgs &a, bool commit) {
     const int64_t units = static_cast<int64_t>(a.batch) * a.nheads;
-    if (a.L > 32) return true;
+    if (a.L > 32 || a.batch > 65535) return true;
     if (commit) return a.L > 4 || units < 1024;
     if (a.dstate == 128) return a.L > 16 ? units > 128 : a.L > 8 && units >= 2048;
     return a.L > (a.dstate == 16 && units >= 2048 ? 12 : 8) || units < 1024;

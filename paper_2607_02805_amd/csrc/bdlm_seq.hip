@@ -1200,8 +1200,10 @@ bool one_segment(const LaunchArgs &a, int64_t T, int64_t block_len) {
 // 0.97, 512 1.15; 32, 320 tokens 0.96, 512 1.04; 16, all within 0.95 to 1.05 from 192; bf16
 // dstate 128, 640 tokens 0.99, 1,024 1.14; 64 and 32, 384 tokens 0.96, 1,024 1.2 and 1.1; 16,
 // 128 tokens 0.92, 256 1.06, 512 1.15 (to 1,536 row-heads 256 tokens 0.87 to 1.03).
+// (The combination has a thread per state quad, and a launch holds fewer than 2^32 threads.)
 bool prefill_in_one(const LaunchArgs &a, int64_t T) {
     const int64_t units = static_cast<int64_t>(a.batch) * a.nheads;
+    if (units * (kP * a.dstate / 4) >= int64_t(1) << 32) return true;
     if (a.bf16) {
         if (a.dstate == 16) return T <= (units > 1536 ? 128 : 256);
         return T <= (a.dstate == 128 ? 640 : 384);

@@ -161,6 +161,9 @@ def test_prefill_without_outputs(rules, N, bf16):
     """Longer prompts run as the states pass and the combination, as they did before."""
     for units, most in IN_ONE[N, bf16]:
         assert rules("in_one", units, 1, 1, most, N, bf16) and not rules("in_one", units, 1, 1, most + 1, N, bf16)
+    quads = 64 * N // 4                                  # threads of the combination per row-head
+    for units in (((1 << 32) - 1) // quads, (1 << 32) // quads):
+        assert rules("in_one", units, 1, 1, 2000, N, bf16) == (units * quads >= 1 << 32)
 
 
 @pytest.mark.parametrize("N", [16, 32, 64, 128])
@@ -205,6 +208,8 @@ def test_short_convolution_blocks(rules, N):
             return rules("pays", units, 1, 1, L, N, 0, last=commit)
         for L in (33, 64, 65, 256):
             assert pays(0, L) and pays(1, L)
+        for L in (1, 8, 16):                             # rows are a grid dimension there
+            assert rules("pays", 65536, units, 1, L, N, 0) and rules("pays", 65536, units, 1, L, N, 0, last=1)
         for L in (1, 4, 5, 8, 9, 12, 13, 16, 17, 32):
             assert pays(1, L) == (L > 4 or units < 1024)
             if N == 128:
