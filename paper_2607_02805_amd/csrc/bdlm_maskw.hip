@@ -550,7 +550,10 @@ bdlm_mask_window_kernel(const WindowArgs a) {
         for (int pt = 0; pt < 4; ++pt) {
 #pragma unroll
             for (int s = 0; s < NSET; ++s) Y[m][pt] += skip[s] * quad_val(as_s16x4(xs[s][m][pt]));
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, Y[m][pt]), rY, yo, 64 * pt, 0);
+            // (the whole offset per lane: a 16-byte store whose offset is partly in a scalar register
+            // may still be reading its data while the next instruction overwrites them, and the
+            // compiler leaves no wait state there)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, Y[m][pt]), rY, yo + 64 * pt, 0, 0);
         }
     }
 }

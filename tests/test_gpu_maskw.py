@@ -63,3 +63,19 @@ def test_one_input_set(N, L, slotted, want_y):
     assert rel_err(got[slots], s_ref) <= REL_TOL
     rest = [i for i in range(batch + 1) if i not in slots]
     np.testing.assert_array_equal(got[rest], from_pool(pool_dev(pool))[rest])
+
+
+@pytest.mark.parametrize("N", [16, 32])
+@pytest.mark.parametrize("H,L", [(4, 256), (32, 200)])
+def test_separate_inputs_repeat(N, H, L):
+    """Thirty calls on the same inputs are equal bit for bit, with two workgroups on a CU (the
+    outputs' stores once let four lanes of sixteen go wrong now and then)."""
+    import paper_2607_02805_amd as bd
+    w = bi.Workload("t", 448 // H, H, 64, N, 1, L, 0, True, 1, 9100 + N + L)
+    f, r = to_dev(bi.block_inputs(w, 0)), to_dev(bi.block_inputs(w, 1))
+    h = pool_dev(bi.random_state(w, 448 // H, 6, 0.5))
+    fwd = (f["x"], f["dt"], f["A"], f["B"], f["C"], f["D"])
+    rev = (r["x"], r["dt"], f["A"], r["B"], r["C"], f["D_rev"])
+    first = bd.scan_block_step_sep(fwd, rev, h)
+    for _ in range(29):
+        assert torch.equal(bd.scan_block_step_sep(fwd, rev, h), first)
