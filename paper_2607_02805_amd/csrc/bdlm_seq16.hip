@@ -358,7 +358,9 @@ __global__ void __launch_bounds__(kThreads * HPW, HPW == 2 ? 4 : (MODE == kPre ?
                 sLa[lane] = ex2(cs - Em);
                 sLb[lane] = ex2(E - cs) * dtv;
                 if constexpr (FULL) {
-                    const float ex = cs - l2;
+                    // the exclusive sum is the token before's inclusive one (not cs - l2, which would
+                    // round once more at the sum's size: a third of the weights' error)
+                    const float ex = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(cs), 0x138, 0xf, 0xf, true));
                     sEx[lane] = ex;
                     sUa[lane] = ex2(E - ex);
                     sUb[lane] = ex2(ex - Em) * dtv;

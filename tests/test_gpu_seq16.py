@@ -87,3 +87,31 @@ def test_boundary_states_in_one_segment(B, H, N, L, K):
             ys.append(yk)
         assert rel_err(pick(y, rows, heads), np.concatenate(ys, 1)) <= REL_TOL
     assert not got[:, 0].any()
+
+
+def test_reverse_weights_after_a_strong_decay():
+    """A token whose decay is 2^-131072 leaves sums whose unit in the last place is 2^-6; the
+    tokens after it decay by 1.5 such units each.  The weight of a later token on an earlier one of
+    its tile is 2^(difference of two sums); each sum is rounded once, so the exponent is within one
+    unit (half a unit more for the weights' own roundings, far less than that)."""
+    import paper_2607_02805_amd as bd
+    log2e, a = np.float32(1.4426950408889634), np.float32(-0.6931472)
+    for _ in range(8):
+        if a * log2e == np.float32(-1):
+            break
+        a = np.nextafter(a, np.float32(-1 if a * log2e > -1 else 0))
+    assert a * log2e == np.float32(-1)
+    T, N, unit = 64, 16, 2.0 ** -6
+    for j in (40, 47, 58, 63):
+        x, dt = torch.zeros(1, T, 1, 64), torch.full((1, T, 1), 1.5 * unit)
+        x[0, j], dt[0, 0] = 1.0, 131072.0
+        B, C = torch.zeros(1, T, 1, N), torch.zeros(1, T, 1, N)
+        B[..., 0] = C[..., 0] = 1.0
+        v = [t.to(torch.bfloat16).to(DEV) for t in (x, dt, B, C)]
+        z = torch.zeros(1, device=DEV)
+        y = bd.scan_full_window(v[0], v[1], torch.tensor([float(a)], device=DEV), v[2], v[3], z, z)
+        t = np.arange(j // 16 * 16, j)
+        got = np.log2(y[0, t, 0, 0].double().cpu().numpy() / (1.5 * unit))
+        off = np.abs(got + 1.5 * unit * (j - t)) / unit
+        print("exponents off by units", off.round(2).tolist(), flush=True)
+        assert off.max() <= 1.25
